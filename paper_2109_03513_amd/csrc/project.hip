@@ -11,8 +11,8 @@
 // exponent minus 127 is the ESB exponent field and the kept fraction bits are
 // the ESB fraction field.
 //
-// Fast path: esb_code_fast / code4 in the internal header (shared with the
-// fused contraction epilogue), the exact esb_code near cell midpoints.
+// Fast path: code4_cvt / esb_code_fast in the internal header (shared with the
+// fused contraction epilogues), the exact esb_code near cell midpoints.
 // HBM bound: 4 B read + 1 B written per element.
 #include "esb_internal.h"
 
@@ -26,6 +26,12 @@ ProjParams proj_params(const Fmt& f) {
     p.c_bits = f.c_bits;
     p.sign_bit = f.sign_bit;
     p.one = 1u << f.k;
+    // the binades 2^0 .. 2^(N-1) fit above 2^-14 (E5M2, up to 2^15) or 2^-6 (E4M3, up to
+    // 1.75 2^8: one binade less)
+    p.cvt = f.k == 2 && f.N <= 29 ? 1u : (f.k == 3 && f.N <= 14 ? 2u : 0u);
+    p.cvt_shift = 8u - (uint32_t)f.n;
+    p.cvt_scale = p.cvt == 1u ? 0x1p-14f : 0x1p-6f;
+    p.cvt_c = f.C * p.cvt_scale;
     return p;
 }
 

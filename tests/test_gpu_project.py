@@ -112,6 +112,27 @@ def test_project_near_scaled_midpoints(esb, b, ks):
         np.testing.assert_array_equal(got, oracle.project(x, alpha, b, ks))
 
 
+@pytest.mark.parametrize("b,ks", [(4, 3), (5, 3), (6, 3), (7, 3), (5, 4), (6, 4), (7, 4), (8, 4)])
+def test_project_one_close_value_per_group(esb, b, ks):
+    """One value within +-40 ulps of a scaled midpoint per group of four (the others far from
+    any): the formats whose codes come from the fp8 conversions, at the width of their margin."""
+    r = np.random.default_rng([43, b, ks])
+    v = oracle.valueset(b, ks)
+    mids = ((v[1:] + v[:-1]) / 2)
+    for alpha in [1.0, 0.7, 1.0 / 3, 2.9, 1e-3, 2.0 ** -100, 2.0 ** 100, 2.0 ** 101]:
+        alpha = np.float32(alpha)
+        base = (mids * np.float64(alpha)).astype(np.float32)
+        steps = np.arange(-40, 41, dtype=np.int64)
+        bits = (base.view(np.uint32).astype(np.int64)[:, None] + steps[None, :]).ravel()
+        x = np.zeros((bits.size, 4), dtype=np.float32)
+        x[:, 0] = bits.astype(np.uint32).view(np.float32)
+        x[:, 1:] = r.choice(v, size=(bits.size, 3)) * alpha
+        x *= r.choice([-1.0, 1.0], size=x.shape).astype(np.float32)
+        x = r.permuted(x, axis=1).ravel()
+        got = host(esb.esb_project(dev(x), scalar(float(alpha)), b, ks))
+        np.testing.assert_array_equal(got, oracle.project(x, alpha, b, ks))
+
+
 def test_project_extreme_scales(esb):
     """Scales outside [2^-125, 2^125] use the exact division for every element."""
     z = np.random.default_rng(9).standard_normal(4096)
