@@ -398,6 +398,47 @@ struct DecodeInfo {
 };
 DecodeInfo decode_info(const Fmt& f);
 
+__device__ __forceinline__ int decode_one(uint32_t c, const DecodeInfo& d) {
+    c &= (1u << d.n) - 1u;
+    const uint32_t s = (c >> (d.n - 1)) & 1u;
+    const uint32_t e = (c >> d.k) & (uint32_t)d.emax;
+    const uint32_t f = c & ((1u << d.k) - 1u);
+    const int m = (e == (uint32_t)d.emax) ? (int)f : (int)(((1u << d.k) | f) << e);
+    return s ? -m : m;
+}
+
+// Four codes (one per byte) to four int8 integers, a format of MODE bits (3, 4 or 5).
+template <int MODE>
+__device__ __forceinline__ uint32_t decode4_lut(uint32_t w, const DecodeInfo& d) {
+    // v_perm_b32 as an 8-entry byte table: selector bytes 0-3 pick bytes of the
+    // second source, 4-7 bytes of the first.
+    const uint32_t sel = w & 0x07070707u;
+    const uint32_t r0 = __builtin_amdgcn_perm(d.lut[1], d.lut[0], sel);
+    if (MODE == 3) return r0;
+    const uint32_t r1 = __builtin_amdgcn_perm(d.lut[3], d.lut[2], sel);
+    const uint32_t m3 = ((w >> 3) & 0x01010101u) * 0xffu;
+    const uint32_t r01 = (r1 & m3) | (r0 & ~m3);
+    if (MODE == 4) return r01;
+    const uint32_t r2 = __builtin_amdgcn_perm(d.lut[5], d.lut[4], sel);
+    const uint32_t r3 = __builtin_amdgcn_perm(d.lut[7], d.lut[6], sel);
+    const uint32_t r23 = (r3 & m3) | (r2 & ~m3);
+    const uint32_t m4 = ((w >> 4) & 0x01010101u) * 0xffu;
+    return (r23 & m4) | (r01 & ~m4);
+}
+
+// Four codes (one per byte) to four int8 integers.
+__device__ __forceinline__ uint32_t decode4(uint32_t w, const DecodeInfo& d) {
+    if (d.mode == 0) {
+        uint32_t r = 0;
+#pragma unroll
+        for (int b = 0; b < 4; b++) r |= ((uint32_t)decode_one((w >> (8 * b)) & 0xffu, d) & 0xffu) << (8 * b);
+        return r;
+    }
+    if (d.mode == 3) return decode4_lut<3>(w, d);
+    if (d.mode == 4) return decode4_lut<4>(w, d);
+    return decode4_lut<5>(w, d);
+}
+
 struct ConvGeom {   // implicit-GEMM view; a dense row-major A is N=M, H=W=1, R=S=1
     int Nb, H, W, C, pitch, Cg, R, S, sh, sw, ph, pw, P, Q;
 };

@@ -41,39 +41,6 @@ struct GemmParams {
 };
 
 // ------------------------------------------------------------------ decode
-__device__ __forceinline__ int decode_one(uint32_t c, const DecodeInfo& d) {
-    c &= (1u << d.n) - 1u;
-    const uint32_t s = (c >> (d.n - 1)) & 1u;
-    const uint32_t e = (c >> d.k) & (uint32_t)d.emax;
-    const uint32_t f = c & ((1u << d.k) - 1u);
-    const int m = (e == (uint32_t)d.emax) ? (int)f : (int)(((1u << d.k) | f) << e);
-    return s ? -m : m;
-}
-
-// Four codes (one per byte) to four int8 integers.
-__device__ __forceinline__ uint32_t decode4(uint32_t w, const DecodeInfo& d) {
-    if (d.mode == 0) {
-        uint32_t r = 0;
-#pragma unroll
-        for (int b = 0; b < 4; b++) r |= ((uint32_t)decode_one((w >> (8 * b)) & 0xffu, d) & 0xffu) << (8 * b);
-        return r;
-    }
-    // v_perm_b32 as an 8-entry byte table: selector bytes 0-3 pick bytes of the
-    // second source, 4-7 bytes of the first.
-    const uint32_t sel = w & 0x07070707u;
-    const uint32_t r0 = __builtin_amdgcn_perm(d.lut[1], d.lut[0], sel);
-    if (d.mode == 3) return r0;
-    const uint32_t r1 = __builtin_amdgcn_perm(d.lut[3], d.lut[2], sel);
-    const uint32_t m3 = ((w >> 3) & 0x01010101u) * 0xffu;
-    const uint32_t r01 = (r1 & m3) | (r0 & ~m3);
-    if (d.mode == 4) return r01;
-    const uint32_t r2 = __builtin_amdgcn_perm(d.lut[5], d.lut[4], sel);
-    const uint32_t r3 = __builtin_amdgcn_perm(d.lut[7], d.lut[6], sel);
-    const uint32_t r23 = (r3 & m3) | (r2 & ~m3);
-    const uint32_t m4 = ((w >> 4) & 0x01010101u) * 0xffu;
-    return (r23 & m4) | (r01 & ~m4);
-}
-
 // Four codes to the high and low int8 planes of m = 256 * hi + lo.
 __device__ __forceinline__ void decode4_split(uint32_t w, const DecodeInfo& d, uint32_t& hi,
                                               uint32_t& lo) {
