@@ -460,6 +460,8 @@ MmaDecode mma_decode(const Fmt& f, int op);
 // 1 (E4M3), 0 (int8 table) or -1 (not eligible) for this pair of formats and
 // reduction length.
 int mma_choose(const Fmt& fa, const Fmt& fb, int64_t K);
+// Whether E4M3 codes on the fp8 MFMA contract this pair exactly over K products.
+bool mma_e4m3_ok(const Fmt& fa, const Fmt& fb, int64_t K);
 // Layout conditions of the path: 16-byte chunks of codes on both operands.
 bool mma_fits(const ConvGeom& ga, const uint8_t* A, int64_t K, int groups, const uint8_t* B,
               int64_t ldb, int b_layout);
@@ -537,6 +539,16 @@ bool stem_fits(const ConvGeom& g, int K, int groups, const Fmt& fx, const Fmt& f
 hipError_t launch_stem(const ConvGeom& g, const uint8_t* x, const Fmt& fx, const float* alphaX,
                        const uint8_t* w, const Fmt& fw, const float* alphaW, float* y, int PP,
                        int QQ, const Post& post, hipStream_t s);
+
+// Contractions with a short reduction and many rows (1x1 convolutions without padding,
+// dense GEMMs, N x K filters with row pitch ldw), E4M3 in registers.  codes: the outputs
+// are codes.
+bool pw_fits(const ConvGeom& g, int M, int N, int groups, const uint8_t* x, const Fmt& fx,
+             const uint8_t* w, int64_t ldw, const Fmt& fw, bool codes);
+hipError_t launch_pw(const ConvGeom& g, int M, int N, const uint8_t* x, const Fmt& fx,
+                     const float* alphaX, const uint8_t* w, int64_t ldw, const Fmt& fw,
+                     const float* alphaW, int32_t* acc, float* y, int64_t ldc, hipStream_t s,
+                     const Post* post);
 
 // Depthwise convolution (groups == C == K): VALU kernel, HBM bound.
 hipError_t launch_dwconv(const ConvGeom& g, const uint8_t* x, const Fmt& fx, const float* alphaX,

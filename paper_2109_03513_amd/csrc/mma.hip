@@ -1183,15 +1183,18 @@ MmaDecode mma_decode(const Fmt& f, int op) {
     return d;
 }
 
-int mma_choose(const Fmt& fa, const Fmt& fb, int64_t K) {
-    if (fa.n <= 3 && fb.n <= 3) return 0;
+bool mma_e4m3_ok(const Fmt& fa, const Fmt& fb, int64_t K) {
     auto f8ok = [](const Fmt& f) {
         return f.ebits <= 4 && f.k <= 3 && !(f.ebits == 4 && f.k == 3);
     };
-    if (!f8ok(fa) || !f8ok(fb)) return -1;
+    if (!f8ok(fa) || !f8ok(fb)) return false;
     const double p = (double)fa.max_int * (double)fb.max_int;
-    if (p > 4096.0 || (double)K * p >= 16777216.0) return -1;
-    return 1;
+    return p <= 4096.0 && (double)K * p < 16777216.0;
+}
+
+int mma_choose(const Fmt& fa, const Fmt& fb, int64_t K) {
+    if (fa.n <= 3 && fb.n <= 3) return 0;
+    return mma_e4m3_ok(fa, fb, K) ? 1 : -1;
 }
 
 MmaDecode mma_decode_f4(const Fmt& f) {

@@ -1,0 +1,101 @@
+"""The short-reduction kernel (1x1 convolutions, GEMMs with K <= 256) vs the oracle, bit for
+bit: reductions at the edges of its 64-byte steps and of both load widths, rows and channels
+that fill no tile, strided pixels, row pitches beyond K, several channel shares per tile row,
+and every form of the epilogue."""
+import ctypes
+
+import numpy as np
+import pytest
+
+import oracle
+from gpuutil import dev, host, log, scalar
+from paper_2109_03513_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+# N, H, W, C, K, stride, activation format, filter format
+CONVS = [
+    (1, 1, 1, 8, 1, 1, (5, 3), (5, 3)),
+    (1, 7, 5, 24, 30, 1, (5, 3), (5, 3)),
+    (2, 13, 9, 24, 144, 1, (5, 3), (4, 2)),
+    (1, 9, 9, 64, 64, 2, (4, 2), (4, 2)),
+    (3, 6, 7, 72, 33, 1, (3, 2), (3, 1)),
+    (2, 11, 8, 144, 24, 1, (5, 3), (5, 3)),
+    (1, 8, 8, 200, 100, 2, (6, 4), (5, 2)),
+    (1, 5, 7, 256, 1024, 1, (5, 3), (5, 3)),
+    (70, 30, 30, 16, 32, 1, (5, 3), (5, 3)),     # more tiles than waves
+]
+
+
+@pytest.mark.parametrize("N,H,W,C,K,st,fx,fw", CONVS)
+@pytest.mark.parametrize("form", ["sums", "y", "relu_y", "residual", "codes", "all"])
+def test_conv1x1(N, H, W, C, K, st, fx, fw, form):
+    from paper_2109_03513_amd import esb
+    x = wl.random_codes(91, (N, H, W, C), 8)
+    w = wl.random_codes(92, (K, 1, 1, C), 8)
+    aX, aW = 0.37, 0.021
+    s, oacc, oy = oracle.conv2d(x, w, *fx, aX, *fw, aW, stride=(st, st))
+    assert s == 0
+    head = (dev(x), *fx, scalar(aX), dev(w), *fw, scalar(aW))
+    log("conv1x1 %s %s" % ((N, H, W, C, K, st, fx, fw), form))
+    if form in ("sums", "y"):
+        acc, y = esb.esb_conv2d(*head, want_acc=form == "sums", stride=(st, st))
+        if form == "sums":
+            np.testing.assert_array_equal(host(acc), oacc)
+        np.testing.assert_array_equal(host(y), oy)
+        return
+    sd = float(np.std(oy)) or 1.0
+    qa = np.float32(0.4 * sd)
+    r = np.random.default_rng([93, C, K])
+    a = b = res = None
+    if form == "all":
+        a = r.uniform(-0.5, 1.5, K).astype(np.float32)
+        b = (r.standard_normal(K) * 0.3 * sd).astype(np.float32)
+    if form in ("all", "residual"):
+        res = (r.standard_normal(oy.shape) * sd).astype(np.float32)
+    relu = form != "residual"
+    oz, oc = oracle.post(oy.reshape(-1, K), 5, 3, qa, a=a, bias=b,
+                         res=None if res is None else res.reshape(-1, K), relu=relu)
+    amax = scalar(0.0)
+    acc, y, codes = esb.esb_conv2d_post(
+        *head, scalar(qa), 5, 3, a=None if a is None else dev(a), b=None if b is None else dev(b),
+        residual=None if res is None else dev(res), relu=relu, want_acc=form == "all",
+        want_y=form != "codes", want_codes=form in ("codes", "all"), absmax=amax, stride=(st, st))
+    if acc is not None:
+        np.testing.assert_array_equal(host(acc), oacc)
+    if y is not None:
+        np.testing.assert_array_equal(host(y).reshape(-1, K).view(np.uint32), oz.view(np.uint32))
+    if codes is not None:
+        np.testing.assert_array_equal(host(codes).reshape(-1, K), oc)
+    assert host(amax)[0] == np.abs(oz).max()
+
+
+@pytest.mark.parametrize("M,N,K,lda,ldb,ldc,off", [
+    (100, 70, 48, 64, 56, 72, 0), (33, 20, 96, 104, 96, 23, 8), (65, 40, 120, 120, 128, 40, 0),
+    (1, 1, 16, 16, 16, 1, 0)])
+def test_gemm_row_pitches(M, N, K, lda, ldb, ldc, off):
+    """Operands and outputs with row pitches of their own and bases at 8 bytes."""
+    from paper_2109_03513_amd import esb
+    torch = pytest.importorskip("torch")
+    A = wl.random_codes(94, (M, lda), 8)
+    B = wl.random_codes(95, (N, ldb), 8)
+    st, oacc, oy = oracle.gemm(np.ascontiguousarray(A[:, :K]), np.ascontiguousarray(B[:, :K]),
+                               5, 3, 0.37, 5, 3, 0.021)
+    assert st == 0
+    dA = torch.zeros(M * lda + 16, dtype=torch.uint8, device="cuda")[off:off + M * lda]
+    dB = torch.zeros(N * ldb + 16, dtype=torch.uint8, device="cuda")[off:off + N * ldb]
+    dA.copy_(dev(A).reshape(-1))
+    dB.copy_(dev(B).reshape(-1))
+    acc = torch.full((M, ldc), -7, dtype=torch.int32, device="cuda")
+    y = torch.full((M, ldc), -7.0, dtype=torch.float32, device="cuda")
+    a, b = scalar(0.37), scalar(0.021)
+    P = lambda t: ctypes.c_void_p(t.data_ptr())   # noqa: E731
+    for want in ((acc, y), (None, y)):
+        y.fill_(-7.0)
+        esb._check("esb_gemm", esb.lib().esb_gemm(
+            M, N, K, P(dA), lda, 5, 3, P(a), P(dB), ldb, 5, 3, P(b), 0,
+            None if want[0] is None else P(acc), P(y), ldc, esb._stream(None)))
+        np.testing.assert_array_equal(host(y)[:, :N], oy)
+        assert (host(y)[:, N:] == -7.0).all()
+    np.testing.assert_array_equal(host(acc)[:, :N], oacc)
+    assert (host(acc)[:, N:] == -7).all()
