@@ -51,6 +51,7 @@ constexpr int kPatchMax = 40 * 1024;    // bytes of the input patch
 constexpr int kMaxCols = kThreads / 4;  // Q + 2: one thread per 16-byte chunk of a patch row
 constexpr int SLAB = 72;                // fp32 row stride of the epilogue slabs
 constexpr int kMaxFill = 10;            // patch chunks per thread and chunk of channels
+constexpr int kFewFill = 5;             // the same where this many suffice
 constexpr int kWPer = NT * TAPS * 4 / kThreads;   // filter chunks per thread (9)
 static_assert(4 * 32 * SLAB * 4 <= kPatchMax, "epilogue slabs fit the patch");
 static_assert(kWPer * kThreads == NT * TAPS * 4, "whole filter chunks per thread");
@@ -247,19 +248,31 @@ __device__ __forceinline__ uint32_t store_block(const Conv3Params& p, const floa
 // MULTI: more than one chunk of input channels (the filter slices then travel
 // per chunk; at most 4 blocks per tile, for the registers).  ACC: the int32
 // sums are written too (a separate instance: keeping both outputs live costs
-// registers).
-template <int TMB, bool MULTI, bool ACC>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
+// registers).  KG == 2: one workgroup of eight waves per CU, whose two halves take every
+// other chunk of input channels, each with its own patch and filter slice, and add their
+// (exact) sums at the end: where there are no more tiles than CUs, a second workgroup would
+// find no tile, and four waves alone leave fill, barriers and LDS reads uncovered
+// (512 -> 512 at 7 x 7, batch 64, 200 tiles: 28.0 us with KG 1, 25.6 with 2; with four chunks
+// each half has too few of them: 256 -> 256 at 14 x 14, batch 16, 14.4 against 14.8).
+// FILL: patch chunks per thread, at least patch rows / rows per step; the unused ones of a
+// larger FILL cost registers, repeated loads of one place and decoding.
+template <int TMB, bool MULTI, bool ACC, int FILL, int KG = 1>
+__global__ __launch_bounds__(kThreads * KG) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void k_conv3x3(Conv3Params p) {
     constexpr int TM = 32 * TMB;
     constexpr int NMB = TMB >= 8 ? 2 : 1;    // output blocks of a wave: NMB x NNB
     constexpr int NNB = TMB >= 4 ? 2 : 1;
     static_assert(4 * NMB * NNB == 2 * TMB, "four waves cover the tile");
-    static_assert(!MULTI || TMB <= 4, "several chunks: at most 4 pixel blocks");
-    __shared__ __align__(16) uint8_t wlds[NT * WST];
-    __shared__ __align__(16) uint8_t patch[kPatchMax];
-    const int tid = threadIdx.x, lane = tid & 63;
+    static_assert(!MULTI || TMB <= 4 || KG == 2, "several chunks: at most 4 pixel blocks");
+    static_assert(KG == 1 || (MULTI && !ACC), "halves of the reduction: several chunks");
+    __shared__ __align__(16) uint8_t wlds_all[KG][NT * WST];
+    __shared__ __align__(16) uint8_t patch_all[KG][kPatchMax];
+    const int lane = threadIdx.x & 63;
+    const int half = KG == 2 ? __builtin_amdgcn_readfirstlane(threadIdx.x / kThreads) : 0;
+    const int tid = (int)threadIdx.x - half * kThreads;   // within the half
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    uint8_t* const wlds = wlds_all[half];
+    uint8_t* const patch = patch_all[half];
     const int lr = lane & 31, lg = lane >> 5;
     // this wave's blocks: pixel blocks mbw + i (i < NMB), channel blocks nbw + j (j < NNB)
     const int mbw = TMB == 8 ? 2 * wave : (TMB == 4 ? wave : wave >> 1);
@@ -273,7 +286,6 @@ void k_conv3x3(Conv3Params p) {
     const float s = ldexpf(p.alphaX[0] * p.alphaW[0], -(p.kX + p.kW));
     const float qa = post_alpha(p.post);
     uint32_t amax = 0;
-    constexpr int FILL = kMaxFill;
     const int st = p.st;
     const int cols = p.W + 2, PP2 = p.H + 2, PQ = p.P * p.Q;
     // patch fill: thread t takes chunk t % (4 cols) of rows t / (4 cols), + rstep, ...
@@ -299,59 +311,66 @@ void k_conv3x3(Conv3Params p) {
         const int i1 = m1 / PQ, p1 = (m1 - i1 * PQ) / p.Q;
         nrows = i1 * PP2 + st * p1 + 3 - R0;
     };
-    // The codes of one (tile, chunk): this thread's patch chunks (chunk u is row
-    // fri + u rstep; bit u of vmask: inside the input) and, with several chunks,
-    // its filter chunks; every load in flight at once.
+    // This thread's patch chunks of a tile (chunk u is row fri + u rstep): their places in the
+    // input, and in bit u of vmask whether inside it; nfill: chunks that any thread has.
     uint4 raw[FILL], wraw[kWPer];
-    uint32_t vmask = 0;
-    auto fetch = [&](int tile, int ch) {
-        int R0, nrows;
-        rows_of(tile, R0, nrows);
+    uint32_t poff[FILL], vmask = 0;
+    int frows = 0;
+    auto prepare = [&](int tile) {
+        int R0;
+        rows_of(tile, R0, frows);
         const int pr = R0 + fri;
         int n = pr / PP2, hp = pr - n * PP2;             // padded row hp of image n
         vmask = 0;
-        const uint8_t* xc = p.x + CK * ch + 16 * fc;
 #pragma unroll
         for (int u = 0; u < FILL; u++) {
             const int ih = hp - 1;
-            const bool ok = fri < rstep && fri + u * rstep < nrows && col_in && n < p.N &&
+            const bool ok = fri < rstep && fri + u * rstep < frows && col_in && n < p.N &&
                             (unsigned)ih < (unsigned)p.H;
-            const int64_t pix = ok ? ((int64_t)n * p.H + ih) * p.W + iw : 0;
-            raw[u] = *(const uint4*)(xc + pix * p.C);
+            poff[u] = (ok ? ((uint32_t)(n * p.H + ih) * p.W + iw) * (uint32_t)p.C : 0u) + 16 * fc;
             vmask |= ok ? (1u << u) : 0u;
             hp += rstep;
             while (hp >= PP2) { hp -= PP2; n++; }
         }
+    };
+    // The codes of one chunk of channels of the prepared tile and, with several chunks, this
+    // thread's filter chunks (channel tid / 4, 16 bytes of every tap); every load in flight
+    // at once.
+    const uint8_t* const wthr = p.w + (n0 + (tid >> 2)) * wrow + 16 * (tid & 3);
+    uint8_t* const wst = wlds + (tid >> 2) * WST + 16 * (tid & 3);
+    auto fetch = [&](int ch) {
+        const uint8_t* xc = p.x + CK * ch;
+#pragma unroll
+        for (int u = 0; u < FILL; u++) {
+            raw[u] = *(const uint4*)(xc + poff[u]);
+        }
         if (MULTI) {
 #pragma unroll
-            for (int u = 0; u < kWPer; u++) {
-                const int it = tid + u * kThreads;
-                const int k = it / (TAPS * 4), rem = it - k * (TAPS * 4);
-                const int t = rem >> 2, c16 = rem & 3;
-                wraw[u] = *(const uint4*)(p.w + (n0 + k) * wrow + t * p.C + CK * ch + 16 * c16);
-            }
+            for (int u = 0; u < kWPer; u++) wraw[u] = *(const uint4*)(wthr + u * p.C + CK * ch);
         }
     };
     auto store_filter = [&]() {
 #pragma unroll
-        for (int u = 0; u < kWPer; u++) {
-            const int it = tid + u * kThreads;
-            const int k = it / (TAPS * 4), rem = it - k * (TAPS * 4);
-            *(uint4*)&wlds[k * WST + 16 * rem] = dec16(wraw[u], p.dw);
-        }
+        for (int u = 0; u < kWPer; u++) *(uint4*)(wst + 64 * u) = dec16(wraw[u], p.dw);
     };
 
     // ---- one chunk of channels: the filter once per workgroup, already in LDS
     if (!MULTI) {
 #pragma unroll
-        for (int u = 0; u < kWPer; u++) {
-            const int it = tid + u * kThreads;
-            const int k = it / (TAPS * 4), rem = it - k * (TAPS * 4);
+        for (int u = 0; u < kWPer; u++) {   // rows of 576 contiguous bytes
+            const int it = tid + u * kThreads, k = it / (TAPS * 4), rem = it - k * (TAPS * 4);
             wraw[u] = *(const uint4*)(p.w + (n0 + k) * wrow + 16 * rem);
         }
-        store_filter();
+#pragma unroll
+        for (int u = 0; u < kWPer; u++) {
+            const int it = tid + u * kThreads, k = it / (TAPS * 4), rem = it - k * (TAPS * 4);
+            *(uint4*)&wlds[k * WST + 16 * rem] = dec16(wraw[u], p.dw);
+        }
     }
-    if (wg < p.ntm) fetch(wg, 0);
+    if (wg < p.ntm && half < nchunks) {
+        prepare(wg);
+        fetch(half);
+    }
 
     for (int tile = wg; tile < p.ntm; tile += nwg) {
         const int m0 = tile * TM;
@@ -375,24 +394,31 @@ void k_conv3x3(Conv3Params p) {
 #pragma unroll
                 for (int r = 0; r < 16; r++) acc[i][j][r] = 0.0f;
 
-        for (int ch = 0; ch < nchunks; ch++) {
+        for (int c0 = 0; c0 < nchunks; c0 += KG) {
+            const int ch = c0 + half;
+            const bool active = KG == 1 || ch < nchunks;   // the last chunk of an odd number
             __syncthreads();   // the previous chunk's (or tile's) reads of the LDS are done
-            if (fri < rstep) {
+            if (active && fri < rstep) {
 #pragma unroll
                 for (int u = 0; u < FILL; u++) {
                     const int i = fri + u * rstep;
-                    if (i < nrows) {
+                    if (i < frows) {
                         const uint4 v = ((vmask >> u) & 1u) ? dec16(raw[u], p.dx)
                                                             : make_uint4(0u, 0u, 0u, 0u);   // E4M3 +0
                         *(uint4*)&patch[patch_off(i * cols + dcol, fc)] = v;
                     }
                 }
             }
-            if (MULTI) store_filter();
+            if (MULTI && active) store_filter();
             __syncthreads();
             // the next chunk's codes, in flight during this chunk's MFMAs
-            if (ch + 1 < nchunks) fetch(tile, ch + 1);
-            else if (tile + nwg < p.ntm) fetch(tile + nwg, 0);
+            if (ch + KG < nchunks) {
+                fetch(ch + KG);
+            } else if (c0 + KG >= nchunks && tile + nwg < p.ntm && half < nchunks) {
+                prepare(tile + nwg);
+                fetch(half);
+            }
+            if (!active) continue;
 
             // fragments of tap t (B: channel 32 j + lr; A: the patch pixel of tap t)
             auto frags = [&](int t, v8i (&fa)[NMB], v8i (&fb)[NNB]) {
@@ -442,6 +468,64 @@ void k_conv3x3(Conv3Params p) {
         //      write are 32 banks apart) and come back as four consecutive
         //      channels per lane.
         __syncthreads();   // every read of the patch is done: the slabs reuse it
+        if constexpr (KG == 2 && NNB == 1) {
+            // one block per wave: the second half gives its sums to the first
+            if (half) {
+#pragma unroll
+                for (int r = 0; r < 16; r++) ((float*)patch_all[0])[r * kThreads + tid] = acc[0][0][r];
+            }
+            __syncthreads();
+            if (!half) {
+#pragma unroll
+                for (int r = 0; r < 16; r++) acc[0][0][r] += ((const float*)patch)[r * kThreads + tid];
+            }
+            __syncthreads();
+            if (half) continue;   // the next tile's patch fill starts behind a barrier of all waves
+            float* slab = (float*)patch + wave * (32 * SLAB);
+#pragma unroll
+            for (int r = 0; r < 16; r++)
+                slab[(8 * (r >> 2) + 4 * lg + (r & 3)) * SLAB + lr] =
+                    s * ldexpf(acc[0][0][r], p.out_shift);
+            // a wave reads back only what it wrote
+            amax = max(amax, store_block<32, true>(p, slab, SLAB, m0 + 32 * mbw, n0 + 32 * nbw, lane, qa));
+            continue;
+        } else if constexpr (KG == 2) {
+            // each half gives away what the other stores (two pixel blocks per wave: one of
+            // them, else one of the two channel blocks) and adds what it gets
+            constexpr int NX = NMB == 2 ? 2 : 1;             // 32 x 32 blocks given away
+            static_assert(NX * 16 * kThreads * 4 <= kPatchMax, "the blocks fit the patch");
+            float* out = (float*)patch_all[half ^ 1];
+            const float* in = (const float*)patch;
+#pragma unroll
+            for (int x = 0; x < NX; x++) {
+                const v16f v0 = NMB == 2 ? acc[0][x] : acc[0][0], v1 = NMB == 2 ? acc[NMB - 1][x] : acc[0][1];
+#pragma unroll
+                for (int r = 0; r < 16; r++)
+                    out[(x * 16 + r) * kThreads + tid] = half ? v0[r] : v1[r];
+            }
+            __syncthreads();
+            v16f sum[NX];
+#pragma unroll
+            for (int x = 0; x < NX; x++) {
+                const v16f v0 = NMB == 2 ? acc[0][x] : acc[0][0], v1 = NMB == 2 ? acc[NMB - 1][x] : acc[0][1];
+#pragma unroll
+                for (int r = 0; r < 16; r++)
+                    sum[x][r] = (half ? v1[r] : v0[r]) + in[(x * 16 + r) * kThreads + tid];
+            }
+            __syncthreads();
+            float* slab = (float*)patch + wave * (32 * SLAB);
+            constexpr int WC = 32 * NX;
+            const int mrow = m0 + 32 * (mbw + (NMB == 2 ? half : 0)), cc = NMB == 2 ? 0 : 32 * half;
+#pragma unroll
+            for (int x = 0; x < NX; x++)
+#pragma unroll
+                for (int r = 0; r < 16; r++)
+                    slab[(8 * (r >> 2) + 4 * lg + (r & 3)) * SLAB + 32 * x + lr] =
+                        s * ldexpf(sum[x][r], p.out_shift);
+            __syncthreads();
+            amax = max(amax, store_block<WC, true>(p, slab, SLAB, mrow, n0 + cc, lane, qa));
+            continue;
+        }
         float* slab = (float*)patch + wave * (32 * SLAB);
         constexpr int WCOLS = 32 * NNB;              // channels of a wave's blocks
         const int c0 = 32 * nbw;                      // their first column in the tile
@@ -497,7 +581,7 @@ constexpr int kResThreads = 512;
 constexpr int kResFilterMax = 76 * 1024;   // bytes of the resident filter copy
 constexpr int kResFill = 10;               // filter chunks and patch chunks per thread
 
-template <int NNB, bool ACC>
+template <int NNB, bool ACC, int FILL>
 __global__ __launch_bounds__(kResThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void k_conv3x3_res(Conv3Params p) {
     constexpr int NTR = 32 * NNB;              // output channels per workgroup
@@ -556,28 +640,37 @@ void k_conv3x3_res(Conv3Params p) {
         const int i1 = m1 / PQ, p1 = (m1 - i1 * PQ) / p.Q;
         nrows = i1 * PP2 + p1 + 3 - R0;
     };
-    uint4 raw[kResFill];
-    uint32_t vmask = 0;
-    auto fetch = [&](int tile, int ch) {
-        int R0, nrows;
-        rows_of(tile, R0, nrows);
+    uint4 raw[FILL];   // as in k_conv3x3
+    uint32_t poff[FILL], vmask = 0;
+    int frows = 0;
+    auto prepare = [&](int tile) {
+        int R0;
+        rows_of(tile, R0, frows);
         const int pr = R0 + fri;
         int n = pr / PP2, hp = pr - n * PP2;
         vmask = 0;
-        const uint8_t* xc = p.x + CK * ch + 16 * fc;
 #pragma unroll
-        for (int u = 0; u < kResFill; u++) {
+        for (int u = 0; u < FILL; u++) {
             const int ih = hp - 1;
-            const bool ok = fri < rstep && fri + u * rstep < nrows && col_in && n < p.N &&
+            const bool ok = fri < rstep && fri + u * rstep < frows && col_in && n < p.N &&
                             (unsigned)ih < (unsigned)p.P;
-            const int64_t pix = ok ? ((int64_t)n * p.P + ih) * p.Q + iw : 0;
-            raw[u] = *(const uint4*)(xc + pix * p.C);
+            poff[u] = (ok ? ((uint32_t)(n * p.P + ih) * p.Q + iw) * (uint32_t)p.C : 0u) + 16 * fc;
             vmask |= ok ? (1u << u) : 0u;
             hp += rstep;
             while (hp >= PP2) { hp -= PP2; n++; }
         }
     };
-    if (wg < p.ntm) fetch(wg, 0);
+    auto fetch = [&](int ch) {
+        const uint8_t* xc = p.x + CK * ch;
+#pragma unroll
+        for (int u = 0; u < FILL; u++) {
+            raw[u] = *(const uint4*)(xc + poff[u]);
+        }
+    };
+    if (wg < p.ntm) {
+        prepare(wg);
+        fetch(0);
+    }
 
     for (int tile = wg; tile < p.ntm; tile += nwg) {
         const int m0 = tile * TM;
@@ -600,9 +693,9 @@ void k_conv3x3_res(Conv3Params p) {
             __syncthreads();   // the previous chunk's (or tile's) reads of the patch are done
             if (fri < rstep) {
 #pragma unroll
-                for (int u = 0; u < kResFill; u++) {
+                for (int u = 0; u < FILL; u++) {
                     const int i = fri + u * rstep;
-                    if (i < nrows) {
+                    if (i < frows) {
                         const uint4 v = ((vmask >> u) & 1u) ? dec16(raw[u], p.dx)
                                                             : make_uint4(0u, 0u, 0u, 0u);   // E4M3 +0
                         *(uint4*)&patch[patch_off(i * cols + fcol, fc)] = v;
@@ -610,8 +703,12 @@ void k_conv3x3_res(Conv3Params p) {
                 }
             }
             __syncthreads();
-            if (ch + 1 < nchunks) fetch(tile, ch + 1);
-            else if (tile + nwg < p.ntm) fetch(tile + nwg, 0);
+            if (ch + 1 < nchunks) {
+                fetch(ch + 1);
+            } else if (tile + nwg < p.ntm) {
+                prepare(tile + nwg);
+                fetch(0);
+            }
 
             const uint8_t* wb = &wres[boff + CK * ch];
             auto frags = [&](int t, v8i& fa, v8i (&fb)[NNB]) {
@@ -729,13 +826,14 @@ bool tile_fits(int P, int Q, int TM, int H, int W, int st) {
 // CU (half a workgroup per CU with several chunks: every tile streams the filter
 // slices again, so larger tiles halve that traffic per pixel; ResNet18 l4 at batch
 // 64, 200 tiles of 128 pixels against 392 of 64: 33.9 against 35.5 us), else the
-// largest that fits.
+// smallest: one 56 x 56 image with 64 channels takes 10.4 us in 13 tiles of 256
+// pixels and 7.2 in 49 of 64, 256 channels at 14 x 14 16.2 and 13.7.
 int choose_tmb(int64_t M, int ntn, int P, int Q, int H, int W, int st, bool multi) {
     const int cus = num_cus();
     int fit = 0;
     for (int tmb = multi ? 4 : 8; tmb >= 2; tmb >>= 1) {
         if (!tile_fits(P, Q, 32 * tmb, H, W, st)) continue;
-        if (!fit) fit = tmb;
+        fit = tmb;
         if ((M + 32 * tmb - 1) / (32 * tmb) * ntn >= (multi ? cus / 2 : cus)) return tmb;
     }
     return fit;
@@ -761,7 +859,8 @@ bool conv3x3_fits(const ConvGeom& g, int K, int groups, int op, const uint8_t* x
     if (s2 && g.C < 4 * CK) return false;
     if ((uintptr_t)x % 16 || (uintptr_t)w % 16) return false;
     const int64_t M = (int64_t)g.Nb * g.P * g.Q;
-    if ((M + 256) * K >= ((int64_t)1 << 31) || (int64_t)K * TAPS * g.C >= ((int64_t)1 << 31))
+    if ((M + 256) * K >= ((int64_t)1 << 31) || (int64_t)K * TAPS * g.C >= ((int64_t)1 << 31) ||
+        (int64_t)g.Nb * g.H * g.W * g.C >= ((int64_t)1 << 32))
         return false;
     // With several chunks every workgroup decodes its 64 filter rows per chunk and tile:
     // measured faster than the implicit-GEMM kernels only for few output pixels (ResNet18
@@ -810,13 +909,18 @@ hipError_t launch_conv3x3(const ConvGeom& g, int K, const uint8_t* x, const Fmt&
         if (per < 1) per = 1;
         if (per > p.ntm) per = p.ntm;
         const unsigned blocks = (unsigned)(per * p.ntn);
-        if (ntr == 64) {
-            if (acc) k_conv3x3_res<2, true><<<blocks, kResThreads, 0, s>>>(p);
-            else k_conv3x3_res<2, false><<<blocks, kResThreads, 0, s>>>(p);
-        } else {
-            if (acc) k_conv3x3_res<1, true><<<blocks, kResThreads, 0, s>>>(p);
-            else k_conv3x3_res<1, false><<<blocks, kResThreads, 0, s>>>(p);
-        }
+        const int rs = kResThreads / (4 * (g.Q + 2));
+        const bool few = (patch_rows_max(g.P, g.Q, 256, g.H, 1) + rs - 1) / rs <= kFewFill;
+#define ESB_CONV3_LAUNCH(NNB, FILL)                                                       \
+    do {                                                                                  \
+        if (acc) k_conv3x3_res<NNB, true, FILL><<<blocks, kResThreads, 0, s>>>(p);        \
+        else k_conv3x3_res<NNB, false, FILL><<<blocks, kResThreads, 0, s>>>(p);           \
+    } while (0)
+        if (ntr == 64 && few) ESB_CONV3_LAUNCH(2, kFewFill);
+        else if (ntr == 64) ESB_CONV3_LAUNCH(2, kResFill);
+        else if (few) ESB_CONV3_LAUNCH(1, kFewFill);
+        else ESB_CONV3_LAUNCH(1, kResFill);
+#undef ESB_CONV3_LAUNCH
         return hipGetLastError();
     }
     p.ntn = K / NT;
@@ -824,15 +928,34 @@ hipError_t launch_conv3x3(const ConvGeom& g, int K, const uint8_t* x, const Fmt&
     const int tmb = choose_tmb(p.M, p.ntn, g.P, g.Q, g.H, g.W, p.st, multi);
     if (tmb == 0) return hipErrorInvalidValue;
     p.ntm = (p.M + 32 * tmb - 1) / (32 * tmb);
+    // patch chunks per thread: 5 where they suffice (all but wide images), else kMaxFill
+    const int rstep = kThreads / (4 * (g.W + 2));
+    const bool few = (patch_rows_max(g.P, g.Q, 32 * tmb, g.H, p.st) + rstep - 1) / rstep <= kFewFill;
+    // the reduction in two halves (see k_conv3x3): one tile per CU at most, six chunks or more
+    if (!acc && g.C >= 6 * CK && (int64_t)p.ntm * p.ntn <= num_cus()) {
+        const unsigned blocks = (unsigned)(p.ntm * p.ntn);
+#define ESB_CONV3_LAUNCH(TMB, FILL) k_conv3x3<TMB, true, false, FILL, 2><<<blocks, 2 * kThreads, 0, s>>>(p)
+        if (tmb == 4 && few) ESB_CONV3_LAUNCH(4, kFewFill);
+        else if (tmb == 4) ESB_CONV3_LAUNCH(4, kMaxFill);
+        else if (few) ESB_CONV3_LAUNCH(2, kFewFill);
+        else ESB_CONV3_LAUNCH(2, kMaxFill);
+#undef ESB_CONV3_LAUNCH
+        return hipGetLastError();
+    }
     // persistent workgroups, a whole number per channel tile, two per CU
     int per = (num_cus() * 2) / p.ntn;
     if (per < 1) per = 1;
     if (per > p.ntm) per = p.ntm;
     const unsigned blocks = (unsigned)(per * p.ntn);
+#define ESB_CONV3_LAUNCH2(TMB, MULTI, FILL)                                          \
+    do {                                                                             \
+        if (acc) k_conv3x3<TMB, MULTI, true, FILL><<<blocks, kThreads, 0, s>>>(p);   \
+        else k_conv3x3<TMB, MULTI, false, FILL><<<blocks, kThreads, 0, s>>>(p);      \
+    } while (0)
 #define ESB_CONV3_LAUNCH(TMB, MULTI)                                                 \
     do {                                                                             \
-        if (acc) k_conv3x3<TMB, MULTI, true><<<blocks, kThreads, 0, s>>>(p);         \
-        else k_conv3x3<TMB, MULTI, false><<<blocks, kThreads, 0, s>>>(p);            \
+        if (few) ESB_CONV3_LAUNCH2(TMB, MULTI, kFewFill);                            \
+        else ESB_CONV3_LAUNCH2(TMB, MULTI, kMaxFill);                                \
     } while (0)
     if (!multi && tmb == 8) ESB_CONV3_LAUNCH(8, false);
     else if (!multi && tmb == 4) ESB_CONV3_LAUNCH(4, false);
@@ -840,6 +963,7 @@ hipError_t launch_conv3x3(const ConvGeom& g, int K, const uint8_t* x, const Fmt&
     else if (tmb == 4) ESB_CONV3_LAUNCH(4, true);
     else ESB_CONV3_LAUNCH(2, true);
 #undef ESB_CONV3_LAUNCH
+#undef ESB_CONV3_LAUNCH2
     return hipGetLastError();
 }
 

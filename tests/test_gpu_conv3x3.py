@@ -163,3 +163,43 @@ def test_conv3x3_direct_random_shapes(esb, st, Nb, H, W, C, K):
                             stride=sd, pad=(1, 1), want_acc=True)
     np.testing.assert_array_equal(host(acc), acc_o)
     np.testing.assert_array_equal(host(y).view(np.uint32), y_o.view(np.uint32))
+
+
+# stride, N, H, W, C, K
+HALVED = [
+    (1, 1, 7, 7, 384, 64),       # six chunks: three per half; one 64-pixel tile
+    (1, 2, 5, 6, 448, 128),      # seven: the second half idles in the last round
+    (1, 3, 9, 13, 576, 64),      # nine, ragged last tile
+    (2, 2, 14, 14, 512, 128),    # stride 2
+    (1, 1, 3, 60, 384, 64),      # wide rows: more patch chunks per thread
+    (1, 50, 7, 7, 512, 448),     # 128-pixel tiles, two channel blocks per wave
+    (1, 8, 3, 60, 384, 704),     # 128-pixel tiles, wide rows
+]
+
+
+@pytest.mark.parametrize("st,Nb,H,W,C,K", HALVED)
+@pytest.mark.parametrize("form", ["plain", "all"])
+def test_conv3x3_halved_reduction(esb, st, Nb, H, W, C, K, form):
+    """Six or more chunks of input channels with at most one tile per CU: the two halves of a
+    workgroup share the chunks and add their sums."""
+    x = wl.random_codes(7000 + H + C, (Nb, H, W, C), 5)
+    w = wl.random_codes(7100 + W + K, (K, 3, 3, C), 5)
+    sd = (st, st)
+    status, _, y_o = oracle.conv2d(x, w, 5, 3, ALPHA_X, 5, 3, ALPHA_W, stride=sd, pad=(1, 1))
+    assert status == 0
+    log("conv3x3 halved stride %d %s %s" % (st, (Nb, H, W, C, K), form))
+    head = (dev(x), 5, 3, scalar(ALPHA_X), dev(w), 5, 3, scalar(ALPHA_W))
+    if form == "plain":
+        _, y = esb.esb_conv2d(*head, stride=sd, pad=(1, 1), want_acc=False)
+        np.testing.assert_array_equal(host(y).view(np.uint32), y_o.view(np.uint32))
+        return
+    a, b, res, relu, qa = post_params(9, y_o, K, "all")
+    z_o, codes_o = oracle.post(y_o.reshape(-1, K), 5, 3, qa, a=a, bias=b, res=res.reshape(-1, K),
+                               relu=relu)
+    amax = scalar(0.0)
+    _, y, codes = esb.esb_conv2d_post(*head, scalar(qa), 5, 3, a=dev(a), b=dev(b),
+                                      residual=dev(res), relu=relu, stride=sd, pad=(1, 1),
+                                      want_codes=True, want_y=True, absmax=amax)
+    np.testing.assert_array_equal(host(y).reshape(-1, K).view(np.uint32), z_o.view(np.uint32))
+    np.testing.assert_array_equal(host(codes).reshape(-1, K), codes_o)
+    assert host(amax)[0] == np.max(np.abs(z_o))
