@@ -169,13 +169,14 @@ __device__ __forceinline__ uint32_t wave_scan_or(uint32_t v) {
     v |= dpp<0x143, 0xc>(0u, v);
     return v;
 }
-__device__ __forceinline__ uint32_t lane63(uint32_t v) {
-    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+// The value of lane l (the same in every lane of the wave).
+__device__ __forceinline__ uint32_t lane_of(uint32_t v, int l) {
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, l);
 }
-__device__ __forceinline__ double lane63(double v) {
+__device__ __forceinline__ double lane_of(double v, int l) {
     const uint64_t b = (uint64_t)__double_as_longlong(v);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, 63);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), 63);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, l);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), l);
     return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
 }
 
@@ -282,6 +283,10 @@ inline int plan_lbins(int A) { return hist_lbins(A, true); }
 // of |*gscale|) and the grid-only tables come from this plan when E is inside
 // its range (else they are rebuilt as without a plan).  plan_out: build a plan
 // (x empty): dump the tables after the set-up and return.
+// TPT: thresholds per thread, at most (A <= 1024 TPT).  The set-up and the epilogue are
+// straight code that runs once, where every unrolled step costs its instruction fetches
+// whether it does work or not: grids of up to 1024 thresholds get their own instance.
+template <int TPT>
 __device__ __forceinline__ void dda_hist_block(const float* __restrict__ x, int64_t len,
                                                const float* __restrict__ grid,
                                                const float* __restrict__ gscale, const DdaArgs a,
@@ -289,7 +294,8 @@ __device__ __forceinline__ void dda_hist_block(const float* __restrict__ x, int6
                                                const uint8_t* __restrict__ plan_in,
                                                uint8_t* __restrict__ plan_out) {
     extern __shared__ __align__(16) unsigned char smem[];
-    const int A = a.A, M = a.M, tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+    const int A = a.A, M = a.M, tid = threadIdx.x, lane = tid & 63;
+    const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int nbins = 1 << a.lbins;
     const uint32_t lcop = (uint32_t)hist_lcopies(A);   // log2 of the histogram copies
     const HistLds hl = hist_lds(A, a.lbins);
@@ -305,7 +311,8 @@ __device__ __forceinline__ void dda_hist_block(const float* __restrict__ x, int6
 
     // ---- 0. requests first: this thread's candidate scales and the first chunk
     //         of x, so that both latencies overlap the clearing of the bins.
-    constexpr int kMaxTpt = kDdaMaxThresholds / kHistThreads;   // thresholds per thread
+    constexpr int kMaxTpt = TPT;
+    static_assert(TPT * kHistThreads <= kDdaMaxThresholds, "thresholds per thread");
     const float gsc = gscale ? *gscale : 1.0f;   // candidates fl32(gsc * grid[j])
     // planned: candidates 2^pe factor_j, 2^(pe-1) <= |gsc| < 2^pe (pe = 0 for 0); a
     // scale that is not finite makes every candidate NaN
@@ -322,15 +329,17 @@ __device__ __forceinline__ void dda_hist_block(const float* __restrict__ x, int6
         use_plan = head_ok && sc_ok && pe >= ph.emin && pe <= ph.emax;
     }
     float al[kMaxTpt];
+    if (!use_plan) {
 #pragma unroll
-    for (int r = 0; r < kMaxTpt; r++) {
-        const int i = tid + r * kHistThreads;
-        float v = 1.0f;
-        if (i < A) {
-            if (plan_in) v = sc_ok ? ldexpf(grid[i / M], pe) : __builtin_nanf("");
-            else v = gscale ? gsc * grid[i / M] : grid[i / M];
+        for (int r = 0; r < kMaxTpt; r++) {
+            const int i = tid + r * kHistThreads;
+            float v = 1.0f;
+            if (i < A) {
+                if (plan_in) v = sc_ok ? ldexpf(grid[i / M], pe) : __builtin_nanf("");
+                else v = gscale ? gsc * grid[i / M] : grid[i / M];
+            }
+            al[r] = v;
         }
-        al[r] = v;
     }
     const bool vec = ((uintptr_t)x & 15) == 0;
     const int64_t e0 = (int64_t)bid * a.rows_pb * kRowElems;
@@ -397,10 +406,10 @@ __device__ __forceinline__ void dda_hist_block(const float* __restrict__ x, int6
         const uint32_t* pu = (const uint32_t*)(plan_in + plan_u_off(ph.G, ph.lbins));
         const uint32_t* pt = (const uint32_t*)(plan_in + plan_th_off(ph.G, ph.A, ph.lbins));
         // every load in flight before the first store (at most 8192 bins, A + 260
-        // bounds and A cell starts: 8, 9 and 8 per thread)
+        // bounds and A cell starts: 8, TPT + 1 and TPT per thread)
         constexpr int kB = (1 << 13) / kHistThreads;
-        constexpr int kU = (kDdaMaxThresholds + kMaxSplits + 4 + kHistThreads - 1) / kHistThreads;
-        constexpr int kT = kDdaMaxThresholds / kHistThreads;
+        constexpr int kU = TPT + 1;   // kMaxSplits + 4 <= kHistThreads
+        constexpr int kT = TPT;
         uint2 ev[kB];
         uint32_t uv[kU], tv[kT];
 #pragma unroll
@@ -572,7 +581,7 @@ __device__ __forceinline__ void dda_hist_block(const float* __restrict__ x, int6
         uint32_t* R = (uint32_t*)KH;                     // [Ap + 1]
         Dp = 0;
         {
-            constexpr int kPerMax = (kDdaMaxThresholds + kMaxSplits + kHistThreads - 1) / kHistThreads;
+            constexpr int kPerMax = TPT + 1;   // kMaxSplits <= kHistThreads
             const int per = (int)((Ap + kHistThreads - 1) / kHistThreads);
             uint32_t uv[kPerMax], nf[kPerMax];
             uint32_t mine = 0;
@@ -762,7 +771,7 @@ __device__ __forceinline__ void dda_hist_block(const float* __restrict__ x, int6
     //         to the spare cells); the top atom Dp is taken from the fp64 sums.
     //         Exclusive prefix sums over atoms 0 .. Dp: P0 (u32) over U, P1
     //         (fp64) over the histogram, once both are read.
-    constexpr int kPerMax = (kDdaMaxThresholds + kMaxSplits + 2 + kHistThreads - 1) / kHistThreads;
+    constexpr int kPerMax = TPT + 1;   // kMaxSplits + 2 <= kHistThreads
     const int per = (int)((Dp + 2u + kHistThreads - 1) / kHistThreads);   // atoms 0 .. Dp+1
     uint32_t c0[kPerMax];
     double c1[kPerMax];
@@ -796,9 +805,16 @@ __device__ __forceinline__ void dda_hist_block(const float* __restrict__ x, int6
             s_u[1][wid] = tc; s_u[2][wid] = fl; s_d[1][wid] = ss; s_d[2][wid] = t1;
         }
         lds_barrier();   // wave totals published; every read of the histogram and U is done
+        // the totals of the waves before this one: a scan over the 16 totals, one per lane
+        static_assert(kHistThreads / 64 == 16, "one row of lanes holds every wave's total");
+        const uint32_t w0 = wave_scan_add(lane < 16 ? s_u[0][lane] : 0u);
+        const double w1 = wave_scan_add(lane < 16 ? s_d[0][lane] : 0.0);
         uint32_t r0 = i0 - m0;
         double r1 = i1 - m1;
-        for (int v = 0; v < wid; v++) { r0 += s_u[0][v]; r1 += s_d[0][v]; }
+        if (wid > 0) {
+            r0 += lane_of(w0, wid - 1);
+            r1 += lane_of(w1, wid - 1);
+        }
         uint32_t* P0 = U;
         double* P1 = (double*)KH;
 #pragma unroll
@@ -814,53 +830,80 @@ __device__ __forceinline__ void dda_hist_block(const float* __restrict__ x, int6
     }
     lds_barrier();
 
-    // ---- 9. per cell (j, c), c >= 1: atoms [start_c, start_{c+1}), the last
-    //         one up to Dp; the top atom joins the cell that holds Dp.  One
-    //         thread per cell writes Q_c S1 and Q_c^2 S0 of the cell; thread j
-    //         then sums the cells of candidate j in order.  Cells are taken
-    //         1024 at a time; the terms live where the bin entries were.
+    // ---- 9. A_j = sum_c Q_c S1(cell c), with cell c >= 1 the atoms [start_c, start_{c+1}) (the
+    //         last one up to Dp; the top atom joins the cell that holds Dp), summed by parts:
+    //         A_j = sum_c (Q_c - Q_{c-1}) S1(atoms from start_c on), B_j likewise with Q^2 and
+    //         S0.  One lane per (j, c) with c = 0 .. M = 2^(n-1) - 1 (c = 0 adds nothing).  Up
+    //         to five bits the M + 1 <= 16 lanes of a candidate share a row of lanes, and DPP
+    //         shifts add them up in order; wider formats go through LDS, 1024 terms at a time,
+    //         where thread j adds the terms of candidate j in order (the terms live where the
+    //         bin entries were).
     {
         const uint32_t* P0 = U;
         const double* P1 = (const double*)KH;
-        double2* T = (double2*)smem;                 // [kHistThreads], 16 KB <= the entries
-        double ssb = 0.0, t1b = 0.0;
-        uint32_t tcb = 0, flb = 0;
-#pragma unroll
-        for (int v = 0; v < kHistThreads / 64; v++) {
-            ssb += s_d[1][v]; t1b += s_d[2][v]; tcb += s_u[1][v]; flb |= s_u[2][v];
-        }
+        // sums over the waves, one wave's value per lane
+        const double ssb = lane_of(wave_scan_add(lane < 16 ? s_d[1][lane] : 0.0), 15);
+        const double t1b = lane_of(wave_scan_add(lane < 16 ? s_d[2][lane] : 0.0), 15);
+        const uint32_t tcb = lane_of(wave_scan_add(lane < 16 ? s_u[1][lane] : 0u), 15);
+        const uint32_t flb = lane_of(wave_scan_or(lane < 16 ? s_u[2][lane] : 0u), 15);
         const uint32_t end = Dp + 1u;
-        double Aj = 0.0, Bj = 0.0;
-        for (int i0 = 0; i0 < A; i0 += kHistThreads) {
-            const int i = i0 + tid;
-            if (i < A) {
-                const int j = i / M, c = i - j * M + 1;
-                const uint32_t st = min(TH[i], end);
-                const uint32_t nx = (c < M) ? min(TH[i + 1], end) : end;
-                const double q = (double)set_value(c, a.k);
-                double d1 = P1[nx] - P1[st];
-                uint32_t d0 = P0[nx] - P0[st];
-                if (st <= Dp && Dp < nx) { d1 += t1b; d0 += tcb; }
-                T[tid] = make_double2(q * d1, (q * q) * (double)d0);
-            }
-            lds_barrier();
-            if (tid < a.G) {
-                const int lo = max(tid * M, i0), hi = min(tid * M + M, i0 + kHistThreads);
-                for (int c = lo; c < hi; c += 4) {     // four reads in flight, sums in order
-                    double2 t[4];
-#pragma unroll
-                    for (int u = 0; u < 4; u++) t[u] = T[min(c + u, hi - 1) - i0];
-#pragma unroll
-                    for (int u = 0; u < 4; u++)
-                        if (c + u < hi) { Aj += t[u].x; Bj += t[u].y; }
+        const double p1e = P1[end];
+        const uint32_t p0e = P0[end];
+        auto term = [&](int j, int c, double& ta, double& tb) {   // c >= 1
+            const uint32_t st = min(TH[j * M + c - 1], end);
+            const double q = (double)set_value(c, a.k), q1 = (double)set_value(c - 1, a.k);
+            double d1 = p1e - P1[st];
+            uint32_t d0 = p0e - P0[st];
+            if (st <= Dp) { d1 += t1b; d0 += tcb; }
+            ta = (q - q1) * d1;
+            tb = (q * q - q1 * q1) * (double)d0;
+        };
+        double* out = part + (int64_t)bid * part_stride(a.G);
+        if (a.n <= 5) {
+            const int mb = a.n - 1, lanes = a.G << mb;
+            for (int i = tid; i < ((lanes + 63) & ~63); i += kHistThreads) {   // whole waves
+                const int j = i >> mb, c = i & M;
+                double ta = 0.0, tb = 0.0;
+                if (i < lanes && c > 0) term(j, c, ta, tb);
+                ta += dpp_f64<0x111, 0xf>(ta);
+                tb += dpp_f64<0x111, 0xf>(tb);
+                if (mb > 1) { ta += dpp_f64<0x112, 0xf>(ta); tb += dpp_f64<0x112, 0xf>(tb); }
+                if (mb > 2) { ta += dpp_f64<0x114, 0xf>(ta); tb += dpp_f64<0x114, 0xf>(tb); }
+                if (mb > 3) { ta += dpp_f64<0x118, 0xf>(ta); tb += dpp_f64<0x118, 0xf>(tb); }
+                if (i < lanes && c == M) {   // the last lane holds the sum of its 2^mb lanes
+                    out[j] = ta;
+                    out[a.G + j] = tb;
                 }
             }
-            lds_barrier();
-        }
-        double* out = part + (int64_t)bid * part_stride(a.G);
-        if (tid < a.G) {
-            out[tid] = Aj;
-            out[a.G + tid] = Bj;
+        } else {
+            double2* T = (double2*)smem;                 // [kHistThreads], 16 KB <= the entries
+            double Aj = 0.0, Bj = 0.0;
+            for (int i0 = 0; i0 < A; i0 += kHistThreads) {
+                const int i = i0 + tid;
+                if (i < A) {
+                    const int j = i / M;
+                    double ta, tb;
+                    term(j, i - j * M + 1, ta, tb);
+                    T[tid] = make_double2(ta, tb);
+                }
+                lds_barrier();
+                if (tid < a.G) {
+                    const int lo = max(tid * M, i0), hi = min(tid * M + M, i0 + kHistThreads);
+                    for (int c = lo; c < hi; c += 4) {     // four reads in flight, sums in order
+                        double2 t[4];
+#pragma unroll
+                        for (int u = 0; u < 4; u++) t[u] = T[min(c + u, hi - 1) - i0];
+#pragma unroll
+                        for (int u = 0; u < 4; u++)
+                            if (c + u < hi) { Aj += t[u].x; Bj += t[u].y; }
+                    }
+                }
+                lds_barrier();
+            }
+            if (tid < a.G) {
+                out[tid] = Aj;
+                out[a.G + tid] = Bj;
+            }
         }
         if (tid == 0) {
             out[2 * a.G] = ssb;
@@ -876,6 +919,7 @@ __device__ __forceinline__ void dda_hist_block(const float* __restrict__ x, int6
 // fixed latency of the set-up, epilogue and finalize dominates, so running
 // them side by side costs about as much as one.
 constexpr int kDdaMaxJobs = 8;
+constexpr int kTptMax = kDdaMaxThresholds / kHistThreads;
 struct DdaJob {
     const float* x;
     int64_t len;
@@ -902,17 +946,18 @@ __device__ __forceinline__ int dda_job_of_block(const DdaBatch& B, int b) {
     return j;
 }
 
+template <int TPT>
 __global__ __launch_bounds__(kHistThreads) void k_dda_hist(DdaBatch B) {
     const int j = dda_job_of_block(B, (int)blockIdx.x);
     const DdaJob& J = B.job[j];
-    dda_hist_block(J.x, J.len, J.grid, J.gscale, J.a, J.part, (int)blockIdx.x - J.blk0, J.plan,
+    dda_hist_block<TPT>(J.x, J.len, J.grid, J.gscale, J.a, J.part, (int)blockIdx.x - J.blk0, J.plan,
                    nullptr);
 }
 
 // One block: the set-up for the candidates factors[j] (scale 1), dumped as a plan.
 __global__ __launch_bounds__(kHistThreads) void k_dda_plan(DdaArgs a, const float* factors,
                                                            uint8_t* plan) {
-    dda_hist_block(nullptr, 0, factors, nullptr, a, nullptr, 0, nullptr, plan);
+    dda_hist_block<kTptMax>(nullptr, 0, factors, nullptr, a, nullptr, 0, nullptr, plan);
 }
 
 // --------------------------------------------------------------------- group
@@ -1105,8 +1150,11 @@ static hipError_t set_lds_attributes() {
     int dev = 0;
     if (hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < 64 &&
         !lds_attr_set[dev].load(std::memory_order_acquire)) {
-        hipError_t e = hipFuncSetAttribute((const void*)k_dda_hist,
+        hipError_t e = hipFuncSetAttribute((const void*)k_dda_hist<1>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, 156 * 1024);
+        if (e != hipSuccess) return e;
+        e = hipFuncSetAttribute((const void*)k_dda_hist<kTptMax>,
+                                hipFuncAttributeMaxDynamicSharedMemorySize, 156 * 1024);
         if (e != hipSuccess) return e;
         e = hipFuncSetAttribute((const void*)k_dda_plan, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 156 * 1024);
@@ -1116,11 +1164,20 @@ static hipError_t set_lds_attributes() {
     return hipSuccess;
 }
 
+// The histogram blocks of a batch (the instance for grids of up to 1024 thresholds where
+// every job has one).
+static void launch_hist(const DdaBatch& B, int nhist, int max_lds, hipStream_t s) {
+    bool small = true;
+    for (int i = 0; i < B.count; i++) small = small && B.job[i].a.A <= kHistThreads;
+    if (small) k_dda_hist<1><<<nhist, kHistThreads, max_lds, s>>>(B);
+    else k_dda_hist<kTptMax><<<nhist, kHistThreads, max_lds, s>>>(B);
+}
+
 static hipError_t launch_batch(DdaBatch& B, int max_lds, int max_fin_threads, int nhist, int ngroups,
                               hipStream_t s) {
     const hipError_t e = set_lds_attributes();
     if (e != hipSuccess) return e;
-    k_dda_hist<<<nhist, kHistThreads, max_lds, s>>>(B);
+    launch_hist(B, nhist, max_lds, s);
     if (ngroups > 0) k_dda_group<<<ngroups, 256, 0, s>>>(B);
     k_dda_finalize<<<B.count, max_fin_threads, 0, s>>>(B);
     return hipGetLastError();
@@ -1190,7 +1247,7 @@ hipError_t launch_dda_quantize(const DdaJobDesc& d, uint8_t* codes, hipStream_t 
     }
     hipError_t e = set_lds_attributes();
     if (e != hipSuccess) return e;
-    k_dda_hist<<<nhist, kHistThreads, max_lds, s>>>(B);
+    launch_hist(B, nhist, max_lds, s);
     if (ngroups > 0) k_dda_group<<<ngroups, 256, 0, s>>>(B);
     k_dda_project<<<(unsigned)(tiles > 0 ? tiles : 1), 256, 0, s>>>(B, d.x, d.len, proj_params(d.f),
                                                                     codes);
