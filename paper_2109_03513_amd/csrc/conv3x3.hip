@@ -73,6 +73,7 @@ struct Conv3Params {
     int ntm, ntn;              // pixel tiles, channel tiles
     int out_shift;             // acc = fl32 sum * 2^out_shift
     int kX, kW;
+    int direct;                // outputs straight from the registers: 1 fp32, 2 codes, 0 neither
 };
 
 __device__ __forceinline__ uint32_t dec8(uint32_t c, const MmaDecode& d) {
@@ -87,6 +88,29 @@ __device__ __forceinline__ uint4 dec16(uint4 v, const MmaDecode& d) {
 // LDS byte offset of chunk c (0..3) of patch pixel pix.
 __device__ __forceinline__ int patch_off(int pix, int c) {
     return (pix << 6) | ((c ^ ((pix >> 2) & 3)) << 4);
+}
+
+// One 32 x 32 block of accumulators into a slab of rows (pixels) of sl floats at column c0:
+// register 4 g + e is pixel lane % 32, channel 8 g + 4 (lane / 32) + e.
+__device__ __forceinline__ void to_slab(float* slab, int sl, const v16f& a, int c0, int lane, float s,
+                                        int shift) {
+#pragma unroll
+    for (int g = 0; g < 4; g++) {
+        f32x4 v;
+#pragma unroll
+        for (int e = 0; e < 4; e++) v[e] = s * ldexpf(a[4 * g + e], shift);
+        *(f32x4*)(slab + (lane & 31) * sl + c0 + 8 * g + 4 * (lane >> 5)) = v;
+    }
+}
+__device__ __forceinline__ void to_slab_int(float* slab, int sl, const v16f& a, int c0, int lane,
+                                            int shift) {
+#pragma unroll
+    for (int g = 0; g < 4; g++) {
+        v4i v;
+#pragma unroll
+        for (int e = 0; e < 4; e++) v[e] = (int32_t)ldexpf(a[4 * g + e], shift);
+        *(v4i*)(slab + (lane & 31) * sl + c0 + 8 * g + 4 * (lane >> 5)) = v;
+    }
 }
 
 // The outputs of one 32-pixel block from a wave's slab (row stride sl floats,
@@ -243,6 +267,75 @@ __device__ __forceinline__ uint32_t store_block(const Conv3Params& p, const floa
     return amax;
 }
 
+// The outputs of one 32-pixel block (pixels mrow + lr) and NB blocks of 32 channels from c0
+// straight from the accumulators: the filter is the first matrix operand, so register
+// 4 g + e of block j is channel c0 + 32 j + 8 g + 4 lg + e, four consecutive channels per four
+// registers.  fp32 outputs (with a residual already in res, ReLU, max|z|) leave in 16-byte
+// stores; codes, after two swaps of lane halves, 16 per lane.  Against the trip through LDS
+// slabs this saves 2 x 128 bytes of LDS traffic per pixel and channel block and every barrier
+// of the epilogue (batch 64, codes out: 256 channels
+// at 14 x 14 21.5 -> 18.0 us, 128 at 28 x 28 32.0 -> 26.3; fp32 out: 128 at 28 x 28 23.2 -> 20.7,
+// 512 at 7 x 7 21.8 -> 20.6).  z = v + 0 is the affine step with a = 1, b = 0.
+template <int NB>
+__device__ __forceinline__ void load_res(const Conv3Params& p, f32x4 (&res)[4 * NB], int mrow, int c0,
+                                         int lane) {
+    const int m = min(mrow + (lane & 31), p.M - 1);
+    const float* r = p.post.res + (int64_t)m * p.K + c0 + 4 * (lane >> 5);
+#pragma unroll
+    for (int q = 0; q < 4 * NB; q++) res[q] = *(const f32x4*)(r + 8 * q);
+}
+
+template <int NB, int OUT>
+__device__ __forceinline__ uint32_t store_direct(const Conv3Params& p, const v16f (&a)[NB],
+                                                 const f32x4 (&res)[4 * NB], int mrow, int c0, int lane,
+                                                 float s, float qa) {
+    const int m = mrow + (lane & 31), lg = lane >> 5;
+    const bool in = m < p.M;
+    const bool on = p.post.on != 0, relu = p.post.relu != 0;
+    const bool has_res = OUT == 1 && p.post.res != nullptr;
+    uint32_t amax = 0;
+    auto value = [&](int j, int g) {
+        f32x4 z;
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+            z[e] = s * ldexpf(a[j][4 * g + e], p.out_shift);
+            if (on) z[e] = z[e] + 0.0f;
+            if (has_res) z[e] = z[e] + res[4 * j + g][e];
+            if (relu) z[e] = z[e] > 0.0f ? z[e] : 0.0f;
+            amax = max(amax, __float_as_uint(z[e]) & 0x7fffffffu);
+        }
+        return z;
+    };
+    if (OUT == 1) {
+        float* y = p.y + (int64_t)m * p.K + c0 + 4 * lg;
+#pragma unroll
+        for (int j = 0; j < NB; j++)
+#pragma unroll
+            for (int g = 0; g < 4; g++) {
+                const f32x4 z = value(j, g);
+                if (in) *(f32x4*)(y + 32 * j + 8 * g) = z;
+                __builtin_amdgcn_sched_barrier(0);   // four outputs at a time: registers
+            }
+    } else {
+        typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+        const bool ok = alpha_valid(qa), fast = fast_scale(qa);
+        const float r = 1.0f / qa;
+        uint8_t* o = p.post.codes + (int64_t)m * p.K + c0 + 16 * lg;
+#pragma unroll
+        for (int j = 0; j < NB; j++) {
+            uint32_t c[4];
+#pragma unroll
+            for (int g = 0; g < 4; g++)
+                c[g] = ok ? code4(value(j, g), qa, r, fast, p.post.pp) : p.post.pp.zero_code * 0x01010101u;
+            const u32x2 s02 = __builtin_amdgcn_permlane32_swap(c[0], c[2], false, false);
+            const u32x2 s13 = __builtin_amdgcn_permlane32_swap(c[1], c[3], false, false);
+            if (in) *(uint4*)(o + 32 * j) = make_uint4(s02[0], s02[1], s13[0], s13[1]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    return in ? amax : 0u;
+}
+
 // Two waves per SIMD: two workgroups share a CU (LDS 2 x 78 KB).  TMB: 32-pixel
 // blocks per tile (8, 4 or 2; four waves take TMB x 2 blocks of 32 x 32).
 // MULTI: more than one chunk of input channels (the filter slices then travel
@@ -256,7 +349,7 @@ __device__ __forceinline__ uint32_t store_block(const Conv3Params& p, const floa
 // each half has too few of them: 256 -> 256 at 14 x 14, batch 16, 14.4 against 14.8).
 // FILL: patch chunks per thread, at least patch rows / rows per step; the unused ones of a
 // larger FILL cost registers, repeated loads of one place and decoding.
-template <int TMB, bool MULTI, bool ACC, int FILL, int KG = 1>
+template <int TMB, bool MULTI, int OUT, int FILL, int KG = 1>
 __global__ __launch_bounds__(kThreads * KG) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void k_conv3x3(Conv3Params p) {
     constexpr int TM = 32 * TMB;
@@ -264,6 +357,7 @@ void k_conv3x3(Conv3Params p) {
     constexpr int NNB = TMB >= 4 ? 2 : 1;
     static_assert(4 * NMB * NNB == 2 * TMB, "four waves cover the tile");
     static_assert(!MULTI || TMB <= 4 || KG == 2, "several chunks: at most 4 pixel blocks");
+    constexpr bool ACC = OUT == 3;
     static_assert(KG == 1 || (MULTI && !ACC), "halves of the reduction: several chunks");
     __shared__ __align__(16) uint8_t wlds_all[KG][NT * WST];
     __shared__ __align__(16) uint8_t patch_all[KG][kPatchMax];
@@ -386,6 +480,11 @@ void k_conv3x3(Conv3Params p) {
             const int pp = rem / p.Q, q = rem - pp * p.Q;
             pb[i] = (n * PP2 + st * pp - R0) * cols + q;
         }
+        // one chunk: the filter fragments are the same for every tile, and the compiler would
+        // move all nine taps of them into registers (144, spilled); an offset it cannot see
+        // through keeps their reads here
+        int btile = boff;
+        if (!MULTI) asm volatile("" : "+v"(btile));
         v16f acc[NMB][NNB];
 #pragma unroll
         for (int i = 0; i < NMB; i++)
@@ -425,7 +524,7 @@ void k_conv3x3(Conv3Params p) {
                 const int tr = t / 3, ts = t - 3 * tr;
 #pragma unroll
                 for (int j = 0; j < NNB; j++) {
-                    const uint8_t* b = &wlds[boff + 32 * (nbw + j) * WST + 64 * t];
+                    const uint8_t* b = &wlds[btile + 32 * (nbw + j) * WST + 64 * t];
                     const v4i lo = *(const v4i*)b, hi = *(const v4i*)(b + 16);
                     fb[j] = v8i{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
                 }
@@ -450,7 +549,7 @@ void k_conv3x3(Conv3Params p) {
 #pragma unroll
                     for (int j = 0; j < NNB; j++)
                         acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
-                            fa[i], fb[j], acc[i][j], 0, 0, 0, 127, 0, 127);
+                            fb[j], fa[i], acc[i][j], 0, 0, 0, 127, 0, 127);
                 __builtin_amdgcn_sched_barrier(0);
                 if (t + 1 < TAPS) {
 #pragma unroll
@@ -461,12 +560,22 @@ void k_conv3x3(Conv3Params p) {
             }
         }
 
-        // ---- epilogue, one pixel block of each wave at a time: register r of
-        //      block (i, j) is pixel m0 + 32 (mbw + i) + 8 (r / 4) + 4 lg + r % 4,
-        //      channel n0 + 32 (nbw + j) + lr.  The scaled values go through the
-        //      wave's LDS slab (row stride 72 floats: the two lane halves of a
-        //      write are 32 banks apart) and come back as four consecutive
-        //      channels per lane.
+        // ---- epilogue: register r of block (i, j) is pixel m0 + 32 (mbw + i) + lr, channel
+        //      n0 + 32 (nbw + j) + 8 (r / 4) + 4 lg + r % 4.  Straight from the registers
+        //      (store_direct) where the form allows, else the scaled values go through the
+        //      wave's LDS slab (rows of 72 floats) and come back as four consecutive channels
+        //      per lane, one pixel block at a time.
+        if constexpr (KG == 1 && (OUT == 1 || OUT == 2)) {
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < NMB; i++) {
+                f32x4 res[4 * NNB];
+                const int mrow = m0 + 32 * (mbw + i);
+                if (OUT == 1 && p.post.res) load_res<NNB>(p, res, mrow, n0 + 32 * nbw, lane);
+                amax = max(amax, store_direct<NNB, OUT>(p, acc[i], res, mrow, n0 + 32 * nbw, lane, s, qa));
+            }
+            continue;
+        }
         __syncthreads();   // every read of the patch is done: the slabs reuse it
         if constexpr (KG == 2 && NNB == 1) {
             // one block per wave: the second half gives its sums to the first
@@ -481,11 +590,14 @@ void k_conv3x3(Conv3Params p) {
             }
             __syncthreads();
             if (half) continue;   // the next tile's patch fill starts behind a barrier of all waves
+            if constexpr (OUT == 1 || OUT == 2) {
+                f32x4 res[4];
+                if (OUT == 1 && p.post.res) load_res<1>(p, res, m0 + 32 * mbw, n0 + 32 * nbw, lane);
+                amax = max(amax, store_direct<1, OUT>(p, acc[0], res, m0 + 32 * mbw, n0 + 32 * nbw, lane, s, qa));
+                continue;
+            }
             float* slab = (float*)patch + wave * (32 * SLAB);
-#pragma unroll
-            for (int r = 0; r < 16; r++)
-                slab[(8 * (r >> 2) + 4 * lg + (r & 3)) * SLAB + lr] =
-                    s * ldexpf(acc[0][0][r], p.out_shift);
+            to_slab(slab, SLAB, acc[0][0], 0, lane, s, p.out_shift);
             // a wave reads back only what it wrote
             amax = max(amax, store_block<32, true>(p, slab, SLAB, m0 + 32 * mbw, n0 + 32 * nbw, lane, qa));
             continue;
@@ -512,16 +624,18 @@ void k_conv3x3(Conv3Params p) {
                 for (int r = 0; r < 16; r++)
                     sum[x][r] = (half ? v1[r] : v0[r]) + in[(x * 16 + r) * kThreads + tid];
             }
-            __syncthreads();
-            float* slab = (float*)patch + wave * (32 * SLAB);
             constexpr int WC = 32 * NX;
             const int mrow = m0 + 32 * (mbw + (NMB == 2 ? half : 0)), cc = NMB == 2 ? 0 : 32 * half;
+            if constexpr (OUT == 1 || OUT == 2) {
+                f32x4 res[4 * NX];
+                if (OUT == 1 && p.post.res) load_res<NX>(p, res, mrow, n0 + cc, lane);
+                amax = max(amax, store_direct<NX, OUT>(p, sum, res, mrow, n0 + cc, lane, s, qa));
+                continue;
+            }
+            __syncthreads();
+            float* slab = (float*)patch + wave * (32 * SLAB);
 #pragma unroll
-            for (int x = 0; x < NX; x++)
-#pragma unroll
-                for (int r = 0; r < 16; r++)
-                    slab[(8 * (r >> 2) + 4 * lg + (r & 3)) * SLAB + 32 * x + lr] =
-                        s * ldexpf(sum[x][r], p.out_shift);
+            for (int x = 0; x < NX; x++) to_slab(slab, SLAB, sum[x], 32 * x, lane, s, p.out_shift);
             __syncthreads();
             amax = max(amax, store_block<WC, true>(p, slab, SLAB, mrow, n0 + cc, lane, qa));
             continue;
@@ -534,11 +648,7 @@ void k_conv3x3(Conv3Params p) {
             const int mrow = m0 + 32 * (mbw + i);
             if (ACC) {   // the exact integer sums, through the slab as well
 #pragma unroll
-                for (int j = 0; j < NNB; j++)
-#pragma unroll
-                    for (int r = 0; r < 16; r++)
-                        ((int32_t*)slab)[(8 * (r >> 2) + 4 * lg + (r & 3)) * SLAB + 32 * j + lr] =
-                            (int32_t)ldexpf(acc[i][j][r], p.out_shift);
+                for (int j = 0; j < NNB; j++) to_slab_int(slab, SLAB, acc[i][j], 32 * j, lane, p.out_shift);
                 __syncthreads();
 #pragma unroll 1
                 for (int e = 4 * lane; e < 32 * WCOLS; e += 256) {
@@ -557,11 +667,7 @@ void k_conv3x3(Conv3Params p) {
                 __syncthreads();
             }
 #pragma unroll
-            for (int j = 0; j < NNB; j++)
-#pragma unroll
-                for (int r = 0; r < 16; r++)
-                    slab[(8 * (r >> 2) + 4 * lg + (r & 3)) * SLAB + 32 * j + lr] =
-                        s * ldexpf(acc[i][j][r], p.out_shift);
+            for (int j = 0; j < NNB; j++) to_slab(slab, SLAB, acc[i][j], 32 * j, lane, s, p.out_shift);
             __syncthreads();
             amax = max(amax, store_block<WCOLS, NMB == 1>(p, slab, SLAB, mrow, n0 + c0, lane, qa));
             __syncthreads();
@@ -581,9 +687,10 @@ constexpr int kResThreads = 512;
 constexpr int kResFilterMax = 76 * 1024;   // bytes of the resident filter copy
 constexpr int kResFill = 10;               // filter chunks and patch chunks per thread
 
-template <int NNB, bool ACC, int FILL>
+template <int NNB, int OUT, int FILL>
 __global__ __launch_bounds__(kResThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void k_conv3x3_res(Conv3Params p) {
+    constexpr bool ACC = OUT == 3;
     constexpr int NTR = 32 * NNB;              // output channels per workgroup
     constexpr int TM = 256;                    // pixels per tile: block `wave` of 8
     constexpr int SL = NTR + 8;                // slab row stride (floats): two lane halves
@@ -733,7 +840,7 @@ void k_conv3x3_res(Conv3Params p) {
 #pragma unroll
                 for (int j = 0; j < NNB; j++)
                     acc[j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
-                        fa, fb[j], acc[j], 0, 0, 0, 127, 0, 127);
+                        fb[j], fa, acc[j], 0, 0, 0, 127, 0, 127);
                 __builtin_amdgcn_sched_barrier(0);
                 if (t + 1 < TAPS) {
                     fa = na;
@@ -743,19 +850,19 @@ void k_conv3x3_res(Conv3Params p) {
             }
         }
 
-        // ---- epilogue: block `wave` (pixels m0 + 32 wave ..), register r of
-        //      channel block j is pixel + 8 (r / 4) + 4 lg + r % 4, channel
-        //      n0 + 32 j + lr; through the wave's slab, four channels per lane
+        // ---- epilogue of block `wave` (pixels m0 + 32 wave ..), as in k_conv3x3
+        if constexpr (OUT == 1 || OUT == 2) {
+            f32x4 res[4 * NNB];
+            if (OUT == 1 && p.post.res) load_res<NNB>(p, res, m0 + 32 * wave, n0, lane);
+            amax = max(amax, store_direct<NNB, OUT>(p, acc, res, m0 + 32 * wave, n0, lane, s, qa));
+            continue;
+        }
         __syncthreads();   // every read of the patch is done: the slabs reuse it
         float* slab = (float*)(wave < 4 ? patch : spare) + (wave & 3) * (32 * SL);
         const int mrow = m0 + 32 * wave;
         if (ACC) {
 #pragma unroll
-            for (int j = 0; j < NNB; j++)
-#pragma unroll
-                for (int r = 0; r < 16; r++)
-                    ((int32_t*)slab)[(8 * (r >> 2) + 4 * lg + (r & 3)) * SL + 32 * j + lr] =
-                        (int32_t)ldexpf(acc[j][r], p.out_shift);
+            for (int j = 0; j < NNB; j++) to_slab_int(slab, SL, acc[j], 32 * j, lane, p.out_shift);
             __syncthreads();
 #pragma unroll 1
             for (int e = 4 * lane; e < 32 * NTR; e += 256) {
@@ -774,11 +881,7 @@ void k_conv3x3_res(Conv3Params p) {
             __syncthreads();
         }
 #pragma unroll
-        for (int j = 0; j < NNB; j++)
-#pragma unroll
-            for (int r = 0; r < 16; r++)
-                slab[(8 * (r >> 2) + 4 * lg + (r & 3)) * SL + 32 * j + lr] =
-                    s * ldexpf(acc[j][r], p.out_shift);
+        for (int j = 0; j < NNB; j++) to_slab(slab, SL, acc[j], 32 * j, lane, s, p.out_shift);
         __syncthreads();
         amax = max(amax, store_block<NTR, true>(p, slab, SL, mrow, n0, lane, qa));
     }
@@ -899,7 +1002,17 @@ hipError_t launch_conv3x3(const ConvGeom& g, int K, const uint8_t* x, const Fmt&
     p.out_shift = fx.k + fw.k + 12;
     p.kX = fx.k;
     p.kW = fw.k;
-    if (g.C > CK && p.M > kMultiMaxPixels) {   // the resident-filter kernel, one workgroup per CU
+    if (!acc && !p.post.a && !p.post.b) {   // K is a multiple of 64: every row starts aligned
+        if (y && !p.post.codes && (uintptr_t)y % 16 == 0 && (uintptr_t)p.post.res % 16 == 0) p.direct = 1;
+        if (!y && p.post.codes && !p.post.res && (uintptr_t)p.post.codes % 16 == 0) p.direct = 2;
+    }
+    // The resident-filter kernel, one workgroup per CU: several chunks and many pixels; one
+    // chunk too where codes leave (its outputs go straight from the registers, the two-
+    // workgroup kernel's through slabs: 64 -> 64 at 56 x 56, batch 64, 35.5 against 27.4 us;
+    // fp32 outputs 24.6 against 29.5, four times the bytes behind one workgroup).
+    const bool one_res = g.C == CK && p.direct == 2 && p.st == 1 && res_ntr(g.C, K) != 0 &&
+                         res_tile_fits(g.P, g.Q);
+    if ((g.C > CK || one_res) && p.M > kMultiMaxPixels) {
         if (p.st != 1) return hipErrorInvalidValue;
         const int ntr = res_ntr(g.C, K);
         if (ntr == 0 || !res_tile_fits(g.P, g.Q)) return hipErrorInvalidValue;
@@ -913,8 +1026,10 @@ hipError_t launch_conv3x3(const ConvGeom& g, int K, const uint8_t* x, const Fmt&
         const bool few = (patch_rows_max(g.P, g.Q, 256, g.H, 1) + rs - 1) / rs <= kFewFill;
 #define ESB_CONV3_LAUNCH(NNB, FILL)                                                       \
     do {                                                                                  \
-        if (acc) k_conv3x3_res<NNB, true, FILL><<<blocks, kResThreads, 0, s>>>(p);        \
-        else k_conv3x3_res<NNB, false, FILL><<<blocks, kResThreads, 0, s>>>(p);           \
+        if (acc) k_conv3x3_res<NNB, 3, FILL><<<blocks, kResThreads, 0, s>>>(p);           \
+        else if (p.direct == 1) k_conv3x3_res<NNB, 1, FILL><<<blocks, kResThreads, 0, s>>>(p); \
+        else if (p.direct == 2) k_conv3x3_res<NNB, 2, FILL><<<blocks, kResThreads, 0, s>>>(p); \
+        else k_conv3x3_res<NNB, 0, FILL><<<blocks, kResThreads, 0, s>>>(p);               \
     } while (0)
         if (ntr == 64 && few) ESB_CONV3_LAUNCH(2, kFewFill);
         else if (ntr == 64) ESB_CONV3_LAUNCH(2, kResFill);
@@ -934,7 +1049,12 @@ hipError_t launch_conv3x3(const ConvGeom& g, int K, const uint8_t* x, const Fmt&
     // the reduction in two halves (see k_conv3x3): one tile per CU at most, six chunks or more
     if (!acc && g.C >= 6 * CK && (int64_t)p.ntm * p.ntn <= num_cus()) {
         const unsigned blocks = (unsigned)(p.ntm * p.ntn);
-#define ESB_CONV3_LAUNCH(TMB, FILL) k_conv3x3<TMB, true, false, FILL, 2><<<blocks, 2 * kThreads, 0, s>>>(p)
+#define ESB_CONV3_LAUNCH(TMB, FILL)                                                                   \
+    do {                                                                                              \
+        if (p.direct == 1) k_conv3x3<TMB, true, 1, FILL, 2><<<blocks, 2 * kThreads, 0, s>>>(p);       \
+        else if (p.direct == 2) k_conv3x3<TMB, true, 2, FILL, 2><<<blocks, 2 * kThreads, 0, s>>>(p);  \
+        else k_conv3x3<TMB, true, 0, FILL, 2><<<blocks, 2 * kThreads, 0, s>>>(p);                     \
+    } while (0)
         if (tmb == 4 && few) ESB_CONV3_LAUNCH(4, kFewFill);
         else if (tmb == 4) ESB_CONV3_LAUNCH(4, kMaxFill);
         else if (few) ESB_CONV3_LAUNCH(2, kFewFill);
@@ -947,10 +1067,14 @@ hipError_t launch_conv3x3(const ConvGeom& g, int K, const uint8_t* x, const Fmt&
     if (per < 1) per = 1;
     if (per > p.ntm) per = p.ntm;
     const unsigned blocks = (unsigned)(per * p.ntn);
-#define ESB_CONV3_LAUNCH2(TMB, MULTI, FILL)                                          \
-    do {                                                                             \
-        if (acc) k_conv3x3<TMB, MULTI, true, FILL><<<blocks, kThreads, 0, s>>>(p);   \
-        else k_conv3x3<TMB, MULTI, false, FILL><<<blocks, kThreads, 0, s>>>(p);      \
+    // (one chunk with tiles of 128 pixels or more keeps the slabs: its direct instances spill)
+#define ESB_CONV3_LAUNCH2(TMB, MULTI, FILL)                                                    \
+    do {                                                                                       \
+        constexpr bool D = MULTI || TMB == 2;                                                  \
+        if (acc) k_conv3x3<TMB, MULTI, 3, FILL><<<blocks, kThreads, 0, s>>>(p);                \
+        else if (D && p.direct == 1) k_conv3x3<TMB, MULTI, D ? 1 : 0, FILL><<<blocks, kThreads, 0, s>>>(p); \
+        else if (D && p.direct == 2) k_conv3x3<TMB, MULTI, D ? 2 : 0, FILL><<<blocks, kThreads, 0, s>>>(p); \
+        else k_conv3x3<TMB, MULTI, 0, FILL><<<blocks, kThreads, 0, s>>>(p);                    \
     } while (0)
 #define ESB_CONV3_LAUNCH(TMB, MULTI)                                                 \
     do {                                                                             \

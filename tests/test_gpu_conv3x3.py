@@ -203,3 +203,46 @@ def test_conv3x3_halved_reduction(esb, st, Nb, H, W, C, K, form):
     np.testing.assert_array_equal(host(y).reshape(-1, K).view(np.uint32), z_o.view(np.uint32))
     np.testing.assert_array_equal(host(codes).reshape(-1, K), codes_o)
     assert host(amax)[0] == np.max(np.abs(z_o))
+
+
+# stride, N, H, W, C, K: one kernel and tile each
+OUTPUTS = [
+    (1, 1, 11, 13, 64, 64),      # one chunk, 64-pixel tiles, ragged
+    (1, 24, 28, 28, 64, 64),     # one chunk, many pixels: codes on the resident-filter kernel
+    (1, 24, 28, 28, 128, 64),    # resident filter, 64 channels per workgroup, ragged last tile
+    (1, 90, 14, 14, 256, 32 * 6),  # resident filter, 32 channels per workgroup
+    (2, 3, 15, 13, 256, 128),    # several chunks, stride 2
+    (1, 50, 7, 7, 192, 512),     # several chunks, 128-pixel tiles
+    (1, 50, 7, 7, 448, 512),     # halves of the reduction, 128-pixel tiles
+    (1, 2, 5, 7, 384, 64),       # halves, 64-pixel tiles
+]
+
+
+@pytest.mark.parametrize("st,Nb,H,W,C,K", OUTPUTS)
+@pytest.mark.parametrize("form", ["codes", "relu_y", "in_place", "absmax"])
+def test_conv3x3_direct_outputs(esb, st, Nb, H, W, C, K, form):
+    """Outputs that leave straight from the accumulators: codes alone, fp32 with ReLU, a
+    residual that is the output buffer itself; and the maximum alone, which has none."""
+    x = wl.random_codes(8000 + H + C, (Nb, H, W, C), 5)
+    w = wl.random_codes(8100 + W + K, (K, 3, 3, C), 5)
+    sd = (st, st)
+    status, _, y_o = oracle.conv2d(x, w, 5, 3, ALPHA_X, 5, 3, ALPHA_W, stride=sd, pad=(1, 1))
+    assert status == 0
+    r = np.random.default_rng(11)
+    sdev = float(np.std(y_o)) or 1.0
+    qa = np.float32(0.4 * sdev)
+    res = (r.standard_normal(y_o.shape) * sdev).astype(np.float32) if form == "in_place" else None
+    z_o, codes_o = oracle.post(y_o.reshape(-1, K), 5, 3, qa, res=None if res is None else
+                               res.reshape(-1, K), relu=form != "in_place")
+    log("conv3x3 outputs stride %d %s %s" % (st, (Nb, H, W, C, K), form))
+    amax = scalar(0.0)
+    y_in = dev(res) if res is not None else None
+    _, y, codes = esb.esb_conv2d_post(
+        dev(x), 5, 3, scalar(ALPHA_X), dev(w), 5, 3, scalar(ALPHA_W), scalar(qa), 5, 3,
+        residual=y_in, y=y_in, relu=form != "in_place", stride=sd, pad=(1, 1),
+        want_codes=form == "codes", want_y=form == "relu_y", absmax=amax)
+    if form == "codes":
+        np.testing.assert_array_equal(host(codes).reshape(-1, K), codes_o)
+    elif form != "absmax":
+        np.testing.assert_array_equal(host(y).reshape(-1, K).view(np.uint32), z_o.view(np.uint32))
+    assert host(amax)[0] == np.max(np.abs(z_o))
