@@ -25,6 +25,7 @@ ESB_B_NK = 0
 ESB_B_KN = 1
 
 _lib = None
+_torch = None        # torch, once lib() has loaded (its attribute look-ups cost less than an import)
 
 
 class EsbError(RuntimeError):
@@ -62,12 +63,13 @@ class PostDesc(ctypes.Structure):
 
 def lib():
     """Load libesb.so (after torch, so that both share one HIP runtime)."""
-    global _lib
+    global _lib, _torch
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise RuntimeError("libesb.so not built: run paper_2109_03513_amd.build.build()")
         try:
-            import torch  # noqa: F401  (loads torch's HIP runtime first)
+            import torch  # (loads torch's HIP runtime first)
+            _torch = torch
         except ImportError:
             pass
         L = ctypes.CDLL(LIB_PATH)
@@ -135,18 +137,25 @@ def _check(fn, status):
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    """Address of a tensor (or None): what a c_void_p argument takes as it is."""
+    return None if t is None else t.data_ptr()
 
 
 def _stream(stream):
+    """Handle of a stream: an int, an object with .cuda_stream, or the current one for None."""
     if stream is not None:
-        return ctypes.c_void_p(stream if isinstance(stream, int) else stream.cuda_stream)
+        return stream if isinstance(stream, int) else stream.cuda_stream
     import torch
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    try:   # the raw handle, without building a Stream object (which costs several us a call)
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    except AttributeError:
+        return torch.cuda.current_stream().cuda_stream
 
 
 def _dev_tensor(t, dtype, name):
-    import torch
+    torch = _torch
+    if torch is None:
+        import torch
     if not isinstance(t, torch.Tensor) or not t.is_cuda:
         raise TypeError("%s must be a CUDA (HIP) tensor" % name)
     if t.dtype != dtype:
