@@ -1152,10 +1152,17 @@ hipError_t launch_op(const FastParams& g, int groups, hipStream_t s) {
     };
     // Measured on MI355X (ESB(5,3) operands): 256 x 256 on eight waves is the
     // fastest tile wherever it fills the chip; below that, decoding per MAC
-    // grows as (BM + BN) / (BM * BN), so the largest tile that keeps at least
-    // half the CUs busy wins over a smaller one that fills them all.
+    // grows as (BM + BN) / (BM * BN).  A convolution's addresses cost more per
+    // tile row, and the largest tile that keeps at least half the CUs busy wins
+    // (3x3 / 2, 128 -> 256 at 28 x 28, batch 64, 196 tiles of 128 x 128: 17.1 us
+    // against 23.8 in 64 x 64); a dense product with fewer tiles than CUs is faster in
+    // 64 x 64, two workgroups per CU (1999 x 1000 x 2048, 128 tiles: 22.1 against
+    // 19.3 us; 4096 x 500 x 1024 14.2 against 12.2; 2500 x 800 x 496 10.9 against 10.2).
+    const bool dense = g.ga.H == 1 && g.ga.W == 1 && g.ga.R == 1 && g.ga.S == 1;
     if (g.N > 128 && tiles(256, 256) >= cus) return launch_t<256, 256, 2, 4, OP, 2>(g, groups, s);
-    if (g.N > 64 && tiles(128, 128) >= cus / 2) return launch_t<128, 128, 2, 4, OP, 2>(g, groups, s);
+    if (g.N > 64 && tiles(128, 128) >= (dense ? cus : cus / 2))
+        return launch_t<128, 128, 2, 4, OP, 2>(g, groups, s);
+    if (dense && g.N > 64) return launch_t<64, 64, 2, 2, OP, 4>(g, groups, s);
     if (tiles(128, 64) >= cus) return launch_t<128, 64, 2, 2, OP, 4>(g, groups, s);
     return launch_t<64, 64, 2, 2, OP, 4>(g, groups, s);
 }
@@ -1332,7 +1339,9 @@ hipError_t launch_mma_pre(int M, int N, int K, int groups, const ConvGeom& ga, c
         return M > 64 ? launch_pre_t<128, 128, 2, 4, 4>(g, groups, conv, f4, s)
                       : launch_pre_t<64, 64, 2, 2, 4>(g, groups, conv, f4, s);
     if (N > 128 && tiles(256, 256) >= cus) return launch_pre_t<256, 256, 2, 4, 4>(g, groups, conv, f4, s);
-    if (N > 64 && tiles(256, 128) >= cus) return launch_pre_t<256, 128, 4, 2, 4>(g, groups, conv, f4, s);
+    // (256 x 128 tiles in between were slower wherever they applied: 3000 x 3000 x 3008 E2M1
+    // 67.2 us against 52.3 in 128 x 128, E4M3 103.1 against 78.2; 2048 x 4096 x 2048 E4M3
+    // 44.0 against 40.9)
     if (N > 64 && tiles(128, 128) >= cus / 2) return launch_pre_t<128, 128, 2, 4, 4>(g, groups, conv, f4, s);
     if (tiles(128, 64) >= cus) return launch_pre_t<128, 64, 2, 2, 4>(g, groups, conv, f4, s);
     return launch_pre_t<64, 64, 2, 2, 4>(g, groups, conv, f4, s);
@@ -1345,13 +1354,19 @@ hipError_t launch_mma_pre(int M, int N, int K, int groups, const ConvGeom& ga, c
 // batch 128 with 128 x 64 tiles: 4 ranges 24.5 us, 8 ranges 26.3, 16 ranges
 // 36.5; more partial sums cost more than the extra workgroups gain; 128 x 128
 // tiles on eight waves with 8 ranges: 24.0 us); 1 when no split pays.
-int mma_splitk(int64_t M, int64_t N, int64_t K, int* kchunk) {
+int mma_splitk(int64_t M, int64_t N, int64_t K, int* kchunk, bool use) {
     *kchunk = (int)K;
     const int64_t cus = num_cus();
     const int64_t bm = M > 64 ? 128 : 64;
     const int64_t bn = M > 64 ? 128 : 64;
     const int64_t tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
     if (2.0 * (double)M * (double)N * (double)K < 2147483648.0 || tiles * 2 >= cus) return 1;
+    // Tiles of 64 x 64 that give every CU a workgroup need no split (1200 x 1200 x 1200
+    // 27.8 us split, 13.2 not; 800 x 1600 x 4096 37.6 and 30.5), and over a short reduction
+    // half as many do (300 x 3000 x 2048, 235 tiles: 27.2 and 13.2; 500 x 1000 x 4096, 128
+    // tiles, ties at 20.2; 128 x 4096 x 9216, 128 tiles, 23.6 and 41.8 the other way).
+    const int64_t small = ((M + 63) / 64) * ((N + 63) / 64);
+    if (use && (small >= cus || (2 * small >= cus && K < 4096))) return 1;
     int64_t ks = (cus + tiles - 1) / tiles;
     if (ks > K / 256) ks = K / 256;
     if (ks > 16) ks = 16;
@@ -1374,7 +1389,7 @@ hipError_t launch_mma(int op, int M, int N, int K, int groups, const ConvGeom& g
     g.part = nullptr;
     if (part && groups == 1) {
         int kc = K;
-        const int ks = mma_splitk(M, N, K, &kc);
+        const int ks = mma_splitk(M, N, K, &kc, true);
         if (ks > 1) { g.ksplit = ks; g.kchunk = kc; g.part = part; }
     }
     g.da = mma_decode(fa, op);
