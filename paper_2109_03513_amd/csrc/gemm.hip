@@ -41,19 +41,23 @@ struct GemmParams {
 };
 
 // ------------------------------------------------------------------ decode
-// Four codes to the high and low int8 planes of m = 256 * hi + lo.
-__device__ __forceinline__ void decode4_split(uint32_t w, const DecodeInfo& d, uint32_t& hi,
+// Decoding through a 256-entry LDS table of (low byte | high byte << 8) per code, m = 256 * hi
+// + lo with int8 hi, lo (hi is 0 and unused where every |m| <= 127): three operations and one
+// LDS read per code for every format, where arithmetic takes about 20 and byte-permute tables
+// branch on the format per dword (1000 x 1000 x 999: 28.7 us by permutes in ESB(5,2), 15.2
+// by the table).
+__device__ __forceinline__ uint16_t lut_entry(uint32_t c, const DecodeInfo& d) {
+    const int m = decode_one(c, d);
+    const int l = (int)(int8_t)(m & 0xff);
+    return (uint16_t)(((uint32_t)l & 0xffu) | (((uint32_t)((m - l) >> 8) & 0xffu) << 8));
+}
+// Four codes to the high and low int8 planes.
+__device__ __forceinline__ void decode4_table(uint32_t w, const uint16_t* lut, uint32_t& hi,
                                               uint32_t& lo) {
-    hi = 0;
-    lo = 0;
-#pragma unroll
-    for (int b = 0; b < 4; b++) {
-        const int m = decode_one((w >> (8 * b)) & 0xffu, d);
-        const int l = (int)(int8_t)(m & 0xff);
-        const int h = (m - l) >> 8;
-        lo |= ((uint32_t)l & 0xffu) << (8 * b);
-        hi |= ((uint32_t)h & 0xffu) << (8 * b);
-    }
+    const uint32_t p01 = (uint32_t)lut[w & 0xffu] | ((uint32_t)lut[(w >> 8) & 0xffu] << 16);
+    const uint32_t p23 = (uint32_t)lut[(w >> 16) & 0xffu] | ((uint32_t)lut[w >> 24] << 16);
+    lo = __builtin_amdgcn_perm(p23, p01, 0x06040200u);
+    hi = __builtin_amdgcn_perm(p23, p01, 0x07050301u);
 }
 
 __device__ __forceinline__ int swz(int row, int chunk) {
@@ -62,20 +66,15 @@ __device__ __forceinline__ int swz(int row, int chunk) {
 
 template <int P>
 __device__ __forceinline__ void store_tile(int8_t* base, int plane_stride, int row, int chunk,
-                                           uint4 codes, const DecodeInfo& d) {
+                                           uint4 codes, const uint16_t* lut) {
     const int off = swz(row, chunk);
-    if (P == 1) {
-        uint4 v;
-        v.x = decode4(codes.x, d); v.y = decode4(codes.y, d);
-        v.z = decode4(codes.z, d); v.w = decode4(codes.w, d);
-        *(uint4*)(base + off) = v;
-    } else {
-        uint4 h, l;
-        decode4_split(codes.x, d, h.x, l.x); decode4_split(codes.y, d, h.y, l.y);
-        decode4_split(codes.z, d, h.z, l.z); decode4_split(codes.w, d, h.w, l.w);
-        *(uint4*)(base + off) = l;                 // plane 0: low
-        *(uint4*)(base + plane_stride + off) = h;  // plane 1: high
-    }
+    uint4 h = make_uint4(0u, 0u, 0u, 0u), l;
+    decode4_table(codes.x, lut, h.x, l.x);
+    decode4_table(codes.y, lut, h.y, l.y);
+    decode4_table(codes.z, lut, h.z, l.z);
+    decode4_table(codes.w, lut, h.w, l.w);
+    *(uint4*)(base + off) = l;                                // plane 0: low
+    if (P == 2) *(uint4*)(base + plane_stride + off) = h;     // plane 1: high
 }
 
 // ----------------------------------------------------------------- loaders
@@ -172,15 +171,41 @@ __device__ __forceinline__ uint4 a_load1(const ASlot& sl, const GemmParams& g, i
     return make_uint4(w[0], w[1], w[2], w[3]);
 }
 
+// Sixteen codes of a contiguous row at reduction index k, any alignment (K >= 16): one
+// unaligned 16-byte load; past the row's end it is the load of the row's last 16 codes moved
+// down, with +0 codes (z4) behind.
+struct __attribute__((packed)) U4Any { uint32_t v[4]; };
+struct __attribute__((packed)) U1Any { uint32_t v; };
+__device__ __forceinline__ uint4 row_load16(const uint8_t* row, int k, int K, uint32_t z4) {
+    if (k >= K) return make_uint4(z4, z4, z4, z4);
+    const U4Any u = *(const U4Any*)(row + (k + 16 <= K ? k : K - 16));
+    if (k + 16 <= K) return make_uint4(u.v[0], u.v[1], u.v[2], u.v[3]);
+    const int rem = K - k, sh = 8 * (16 - rem);          // rem codes stay: 1 .. 15
+    uint64_t lo = ((uint64_t)u.v[1] << 32) | u.v[0], hi = ((uint64_t)u.v[3] << 32) | u.v[2];
+    if (sh < 64) {
+        lo = (lo >> sh) | (hi << (64 - sh));
+        hi >>= sh;
+    } else {
+        lo = hi >> (sh - 64);
+        hi = 0;
+    }
+    const uint64_t z8 = ((uint64_t)z4 << 32) | z4, ones = ~0ull;
+    const uint64_t ml = rem >= 8 ? 0ull : ones << (8 * rem);
+    const uint64_t mh = rem <= 8 ? ones : ones << (8 * (rem - 8));
+    lo = (lo & ~ml) | (z8 & ml);
+    hi = (hi & ~mh) | (z8 & mh);
+    return make_uint4((uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32));
+}
+
 // B: output-channel row n (within the group), chunk of 16 reduction indices.
-template <int BV>   // 16: NK vector, 1: NK bytes, 2: KN (strided bytes)
+template <int BV>   // 16: NK vector, 4: NK unaligned vector, 1: NK bytes
 __device__ __forceinline__ uint4 b_load(const GemmParams& g, int n, int k_start, int64_t brow0) {
     const uint32_t z4 = g.zeroB * 0x01010101u;
     uint4 v = make_uint4(z4, z4, z4, z4);
     if (n >= g.N || k_start >= g.K) return v;
-    if (BV == 16) {
-        return *(const uint4*)(g.B + (brow0 + n) * g.ldb + k_start);
-    }
+    const uint8_t* row = g.B + (brow0 + n) * g.ldb;
+    if (BV == 16) return *(const uint4*)(row + k_start);
+    if (BV == 4) return row_load16(row, k_start, g.K, z4);
     uint32_t w[4];
 #pragma unroll
     for (int q4 = 0; q4 < 4; q4++) {
@@ -188,14 +213,53 @@ __device__ __forceinline__ uint4 b_load(const GemmParams& g, int n, int k_start,
 #pragma unroll
         for (int b = 0; b < 4; b++) {
             const int kk = k_start + 4 * q4 + b;
-            uint32_t code = g.zeroB;
-            if (kk < g.K)
-                code = (BV == 1) ? g.B[(brow0 + n) * g.ldb + kk] : g.B[(int64_t)kk * g.ldb + brow0 + n];
-            acc |= code << (8 * b);
+            acc |= (kk < g.K ? (uint32_t)row[kk] : g.zeroB) << (8 * b);
         }
         w[q4] = acc;
     }
     return make_uint4(w[0], w[1], w[2], w[3]);
+}
+
+// KN layout: a thread takes blocks of four columns n .. n + 3 by four reduction indices, one
+// dword per reduction index, and turns them around with byte permutes when it stores them.
+__device__ __forceinline__ uint4 b_load_kn(const GemmParams& g, int n, int k_start, int64_t brow0) {
+    const uint32_t z4 = g.zeroB * 0x01010101u;
+    uint32_t w[4];
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+        const int kk = k_start + q;
+        w[q] = z4;
+        if (kk < g.K && n < g.N) {
+            const uint8_t* p = g.B + (int64_t)kk * g.ldb + brow0 + n;
+            if (n + 4 <= g.N) {
+                w[q] = ((const U1Any*)p)->v;
+            } else {
+                for (int b = 0; b < g.N - n; b++)
+                    w[q] = (w[q] & ~(0xffu << (8 * b))) | ((uint32_t)p[b] << (8 * b));
+            }
+        }
+    }
+    return make_uint4(w[0], w[1], w[2], w[3]);
+}
+template <int P>
+__device__ __forceinline__ void store_tile_kn(int8_t* base, int plane_stride, int row, int k4, uint4 r,
+                                              const uint16_t* lut) {
+    const uint32_t a01 = __builtin_amdgcn_perm(r.y, r.x, 0x05010400u);
+    const uint32_t b01 = __builtin_amdgcn_perm(r.w, r.z, 0x05010400u);
+    const uint32_t a23 = __builtin_amdgcn_perm(r.y, r.x, 0x07030602u);
+    const uint32_t b23 = __builtin_amdgcn_perm(r.w, r.z, 0x07030602u);
+    const uint32_t col[4] = {__builtin_amdgcn_perm(b01, a01, 0x05040100u),
+                             __builtin_amdgcn_perm(b01, a01, 0x07060302u),
+                             __builtin_amdgcn_perm(b23, a23, 0x05040100u),
+                             __builtin_amdgcn_perm(b23, a23, 0x07060302u)};
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+        uint32_t h = 0, l;
+        decode4_table(col[j], lut, h, l);
+        const int off = swz(row + j, k4 >> 2) + 4 * (k4 & 3);
+        *(uint32_t*)(base + off) = l;
+        if (P == 2) *(uint32_t*)(base + plane_stride + off) = h;
+    }
 }
 
 // ------------------------------------------------------------------ kernel
@@ -205,7 +269,7 @@ template <int BM, int BN, int WM, int WN, int PA, int PB, int AV, int BV, bool P
 __global__ __launch_bounds__(NT) void k_contract(GemmParams g) {
     static_assert((BM / WM) * (BN / WN) == NT / 64, "4 waves per workgroup");
     constexpr int CA = (BM * 4 + NT - 1) / NT;   // A chunks per thread per stage
-    constexpr int CB = (BN * 4 + NT - 1) / NT;
+    constexpr int CB = (BN * 4 + NT - 1) / NT;   // B chunks, or blocks of 4 x 4 codes (KN)
     constexpr int TI = WM / 16, TJ = WN / 16;
     constexpr int NACC = PA + PB - 1;
     __shared__ __align__(16) int8_t sA[2][PA][BM * BK];
@@ -233,12 +297,20 @@ __global__ __launch_bounds__(NT) void k_contract(GemmParams g) {
         __syncthreads();
         ktab = s_ktab;
     }
+    __shared__ uint16_t s_lutA[256], s_lutB[256];
+    s_lutA[tid] = lut_entry((uint32_t)tid, g.da);
+    s_lutB[tid] = lut_entry((uint32_t)tid, g.db);
+    __syncthreads();
     ASlot as[CA];
+    const uint8_t* arow[CA];   // AV == 4: the slot's row of K contiguous codes
 #pragma unroll
     for (int i = 0; i < CA; i++) {
         const int c = tid + i * NT;
         a_slot_init(as[i], g, m0 + c / 4, c % 4);
         if (c >= BM * 4) as[i].valid = 0;
+        arow[i] = g.A;
+        if (AV == 4 && as[i].valid)
+            arow[i] += (((int64_t)as[i].nimg * g.ga.H + as[i].ih0) * g.ga.W + as[i].iw0) * g.ga.pitch + goffA;
     }
 
     v4i acc[NACC][TI][TJ];
@@ -255,24 +327,36 @@ __global__ __launch_bounds__(NT) void k_contract(GemmParams g) {
         for (int i = 0; i < CA; i++) {
             const int c = tid + i * NT;
             const int kst = k0 + 16 * (c % 4);
-            ra[i] = (AV == 16) ? a_load16(as[i], g, kst, goffA) : a_load1(as[i], g, kst, goffA, ktab);
+            if (AV == 4)
+                ra[i] = row_load16(arow[i], as[i].valid ? kst : g.K, g.K, g.zeroA * 0x01010101u);
+            else
+                ra[i] = (AV == 16) ? a_load16(as[i], g, kst, goffA) : a_load1(as[i], g, kst, goffA, ktab);
         }
 #pragma unroll
         for (int i = 0; i < CB; i++) {
             const int c = tid + i * NT;
-            rb[i] = b_load<BV>(g, n0 + c / 4, k0 + 16 * (c % 4), brow0);
+            if constexpr (BV == 2) {
+                if (c < BN * 4) rb[i] = b_load_kn(g, n0 + 4 * (c % (BN / 4)), k0 + 4 * (c / (BN / 4)), brow0);
+            } else {
+                rb[i] = b_load<BV>(g, n0 + c / 4, k0 + 16 * (c % 4), brow0);
+            }
         }
     };
     auto store_stage = [&](int buf) {
 #pragma unroll
         for (int i = 0; i < CA; i++) {
             const int c = tid + i * NT;
-            if (c < BM * 4) store_tile<PA>(&sA[buf][0][0], BM * BK, c / 4, c % 4, ra[i], g.da);
+            if (c < BM * 4) store_tile<PA>(&sA[buf][0][0], BM * BK, c / 4, c % 4, ra[i], s_lutA);
         }
 #pragma unroll
         for (int i = 0; i < CB; i++) {
             const int c = tid + i * NT;
-            if (c < BN * 4) store_tile<PB>(&sB[buf][0][0], BN * BK, c / 4, c % 4, rb[i], g.db);
+            if (c < BN * 4) {
+                if constexpr (BV == 2)
+                    store_tile_kn<PB>(&sB[buf][0][0], BN * BK, 4 * (c % (BN / 4)), c / (BN / 4), rb[i], s_lutB);
+                else
+                    store_tile<PB>(&sB[buf][0][0], BN * BK, c / 4, c % 4, rb[i], s_lutB);
+            }
         }
     };
     auto advance = [&]() {
@@ -405,23 +489,22 @@ static void launch_t(const GemmParams& g, int groups, hipStream_t s) {
     else k_contract<BM, BN, WM, WN, PA, PB, AV, BV, false><<<grid, NT, 0, s>>>(g);
 }
 
-template <int BM, int BN, int WM, int WN>
-static void launch_fast(const GemmParams& g, int groups, int av, int bv, hipStream_t s) {
+// Loader pairs: A by 16 aligned bytes, 16 unaligned ones of a contiguous row (4) or bytes (1);
+// B the same or KN blocks (2).
+template <int BM, int BN, int WM, int WN, int PA, int PB>
+static void launch_loaders(const GemmParams& g, int groups, int av, int bv, hipStream_t s) {
     if (av == 16) {
-        if (bv == 16) launch_t<BM, BN, WM, WN, 1, 1, 16, 16>(g, groups, s);
-        else if (bv == 1) launch_t<BM, BN, WM, WN, 1, 1, 16, 1>(g, groups, s);
-        else launch_t<BM, BN, WM, WN, 1, 1, 16, 2>(g, groups, s);
+        if (bv == 16) launch_t<BM, BN, WM, WN, PA, PB, 16, 16>(g, groups, s);
+        else if (bv == 2) launch_t<BM, BN, WM, WN, PA, PB, 16, 2>(g, groups, s);
+        else launch_t<BM, BN, WM, WN, PA, PB, 16, 4>(g, groups, s);   // K >= 16 here
+    } else if (av == 4) {
+        if (bv == 2) launch_t<BM, BN, WM, WN, PA, PB, 4, 2>(g, groups, s);
+        else launch_t<BM, BN, WM, WN, PA, PB, 4, 4>(g, groups, s);
     } else {
-        if (bv == 16) launch_t<BM, BN, WM, WN, 1, 1, 1, 16>(g, groups, s);
-        else if (bv == 1) launch_t<BM, BN, WM, WN, 1, 1, 1, 1>(g, groups, s);
-        else launch_t<BM, BN, WM, WN, 1, 1, 1, 2>(g, groups, s);
+        if (bv == 2) launch_t<BM, BN, WM, WN, PA, PB, 1, 2>(g, groups, s);
+        else if (bv == 1) launch_t<BM, BN, WM, WN, PA, PB, 1, 1>(g, groups, s);
+        else launch_t<BM, BN, WM, WN, PA, PB, 1, 4>(g, groups, s);
     }
-}
-
-template <int PA, int PB>
-static void launch_split(const GemmParams& g, int groups, int bv, hipStream_t s) {
-    if (bv == 2) launch_t<64, 64, 32, 32, PA, PB, 1, 2>(g, groups, s);
-    else launch_t<64, 64, 32, 32, PA, PB, 1, 1>(g, groups, s);
 }
 
 hipError_t launch_contraction(int M, int N, int K, int groups, const ConvGeom& ga,
@@ -440,14 +523,20 @@ hipError_t launch_contraction(int M, int N, int K, int groups, const ConvGeom& g
     const bool a16 = (K > 0) && (ga.Cg >= 16) && (ga.Cg % 16 == 0) && (ga.pitch % 16 == 0) &&
                      ((uintptr_t)A % 16 == 0) &&
                      ((int64_t)groups * ga.Cg <= ga.pitch);
+    // Rows of at least 16 contiguous codes that are not aligned take unaligned 16-byte loads
+    // (1000 x 1000 x 999 in ESB(5,2): 71.6 us by single bytes, 15.2 here, and in ESB(6,2) 73.8 and 16.6; KN by 4 x 4 blocks
+    // 2000 x 3000 x 2048 165 -> 84); the byte path stays for convolutions with channels that
+    // are no multiple of 16 and for shorter rows.
     int bv;
     if (b_layout == 1) bv = 2;
-    else bv = ((K > 0) && (K % 16 == 0) && (ldb % 16 == 0) && ((uintptr_t)B % 16 == 0)) ? 16 : 1;
-    const int av = a16 ? 16 : 1;
+    else if (K < 16) bv = 1;
+    else bv = (K % 16 == 0) && (ldb % 16 == 0) && ((uintptr_t)B % 16 == 0) ? 16 : 4;
+    const bool rows = K >= 16 && ga.R == 1 && ga.S == 1 && ga.ph == 0 && ga.pw == 0;
+    const int av = a16 ? 16 : (rows ? 4 : 1);
     if (da.split || db.split) {
-        if (da.split && db.split) launch_split<2, 2>(g, groups, bv, s);
-        else if (da.split) launch_split<2, 1>(g, groups, bv, s);
-        else launch_split<1, 2>(g, groups, bv, s);
+        if (da.split && db.split) launch_loaders<64, 64, 32, 32, 2, 2>(g, groups, av, bv, s);
+        else if (da.split) launch_loaders<64, 64, 32, 32, 2, 1>(g, groups, av, bv, s);
+        else launch_loaders<64, 64, 32, 32, 1, 2>(g, groups, av, bv, s);
         return hipGetLastError();
     }
     // tile choice: the largest tile that still gives every CU a workgroup
@@ -455,9 +544,9 @@ hipError_t launch_contraction(int M, int N, int K, int groups, const ConvGeom& g
     auto tiles = [&](int bm, int bn) {
         return (int64_t)((M + bm - 1) / bm) * ((N + bn - 1) / bn) * groups;
     };
-    if (N > 64 && tiles(128, 128) >= cus) launch_fast<128, 128, 64, 64>(g, groups, av, bv, s);
-    else if (tiles(64, 64) >= cus) launch_fast<64, 64, 32, 32>(g, groups, av, bv, s);
-    else launch_fast<64, 32, 32, 16>(g, groups, av, bv, s);
+    if (N > 64 && tiles(128, 128) >= cus) launch_loaders<128, 128, 64, 64, 1, 1>(g, groups, av, bv, s);
+    else if (tiles(64, 64) >= cus) launch_loaders<64, 64, 32, 32, 1, 1>(g, groups, av, bv, s);
+    else launch_loaders<64, 32, 32, 16, 1, 1>(g, groups, av, bv, s);
     return hipGetLastError();
 }
 
