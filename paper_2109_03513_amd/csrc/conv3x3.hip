@@ -377,7 +377,8 @@ void k_conv3x3(Conv3Params p) {
     const int wg = (int)blockIdx.x / p.ntn, nwg = (int)gridDim.x / p.ntn;
     const int nchunks = MULTI ? p.C / CK : 1;
 
-    const float s = ldexpf(p.alphaX[0] * p.alphaW[0], -(p.kX + p.kW));
+    float s = 0.0f;   // int32 sums alone: the scales may be NULL
+    if (!ACC || p.y || p.post.on) s = ldexpf(p.alphaX[0] * p.alphaW[0], -(p.kX + p.kW));
     const float qa = post_alpha(p.post);
     uint32_t amax = 0;
     const int st = p.st;
@@ -728,7 +729,8 @@ void k_conv3x3_res(Conv3Params p) {
         }
     }
 
-    const float s = ldexpf(p.alphaX[0] * p.alphaW[0], -(p.kX + p.kW));
+    float s = 0.0f;   // int32 sums alone: the scales may be NULL
+    if (!ACC || p.y || p.post.on) s = ldexpf(p.alphaX[0] * p.alphaW[0], -(p.kX + p.kW));
     const float qa = post_alpha(p.post);
     uint32_t amax = 0;
     const int cols = p.Q + 2, PP2 = p.P + 2, PQ = p.P * p.Q;
