@@ -1152,17 +1152,21 @@ hipError_t launch_op(const FastParams& g, int groups, hipStream_t s) {
     };
     // Measured on MI355X (ESB(5,3) operands): 256 x 256 on eight waves is the
     // fastest tile wherever it fills the chip; below that, decoding per MAC
-    // grows as (BM + BN) / (BM * BN).  A convolution's addresses cost more per
-    // tile row, and the largest tile that keeps at least half the CUs busy wins
-    // (3x3 / 2, 128 -> 256 at 28 x 28, batch 64, 196 tiles of 128 x 128: 17.1 us
-    // against 23.8 in 64 x 64); a dense product with fewer tiles than CUs is faster in
-    // 64 x 64, two workgroups per CU (1999 x 1000 x 2048, 128 tiles: 22.1 against
-    // 19.3 us; 4096 x 500 x 1024 14.2 against 12.2; 2500 x 800 x 496 10.9 against 10.2).
+    // grows as (BM + BN) / (BM * BN), and the largest tile that keeps at least
+    // half the CUs busy wins (3x3 / 2, 128 -> 256 at 28 x 28, batch 64, 196 tiles of
+    // 128 x 128: 17.1 us against 23.8 in 64 x 64).  Dense products, whose rows cost no
+    // address arithmetic, are faster in 64 x 64 while these make at most two workgroups
+    // per CU, which run side by side: 1024 x 2048 x 2048 (512 tiles of 64 x 64) 18.3 us
+    // against 20.8.  With a third per CU 1536 x 1536 takes 10.6 against 10.9 at K = 512
+    // (codes out, 1600 x 1600 x 768, 13.3 against 14.0), 14.5 against 14.4 at 1024 and 70.6
+    // against 64.9 at 8192; with a fourth 1920 x 1920 takes 13.7 against 11.8 at 512 and
+    // 92.9 against 64.9 at 8192.
     const bool dense = g.ga.H == 1 && g.ga.W == 1 && g.ga.R == 1 && g.ga.S == 1;
+    const bool small = dense && tiles(64, 64) <= (g.K <= 1024 ? 3 : 2) * cus;
     if (g.N > 128 && tiles(256, 256) >= cus) return launch_t<256, 256, 2, 4, OP, 2>(g, groups, s);
-    if (g.N > 64 && tiles(128, 128) >= (dense ? cus : cus / 2))
+    if (g.N > 64 && !small && tiles(128, 128) >= cus / 2)
         return launch_t<128, 128, 2, 4, OP, 2>(g, groups, s);
-    if (dense && g.N > 64) return launch_t<64, 64, 2, 2, OP, 4>(g, groups, s);
+    if (g.N > 64 && small) return launch_t<64, 64, 2, 2, OP, 4>(g, groups, s);
     if (tiles(128, 64) >= cus) return launch_t<128, 64, 2, 2, OP, 4>(g, groups, s);
     return launch_t<64, 64, 2, 2, OP, 4>(g, groups, s);
 }
