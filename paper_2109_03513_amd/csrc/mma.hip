@@ -1365,12 +1365,22 @@ int mma_splitk(int64_t M, int64_t N, int64_t K, int* kchunk, bool use) {
     const int64_t bn = M > 64 ? 128 : 64;
     const int64_t tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
     if (2.0 * (double)M * (double)N * (double)K < 2147483648.0 || tiles * 2 >= cus) return 1;
-    // Tiles of 64 x 64 that give every CU a workgroup need no split (1200 x 1200 x 1200
-    // 27.8 us split, 13.2 not; 800 x 1600 x 4096 37.6 and 30.5), and over a short reduction
-    // half as many do (300 x 3000 x 2048, 235 tiles: 27.2 and 13.2; 500 x 1000 x 4096, 128
-    // tiles, ties at 20.2; 128 x 4096 x 9216, 128 tiles, 23.6 and 41.8 the other way).
+    // Tiles of 64 x 64 that give every CU a workgroup need no split up to a K where the partial
+    // sums cost less than the longer reduction: with 128 x 128 tiles for a quarter of the
+    // CUs (four ranges, one workgroup per CU) 4096 (1000 x 1000: 22.0 us split, 21.0 not; at
+    // 6144 26.1 and 29.8), 3584 where edges waste a tenth of the tiles (65 x 8192 x 4096
+    // 19.8 and 21.5); with four ranges that overfill the chip 6000 (768 x 1400: 41.3 and 40.7
+    // at 6144, 47.7 and 52.8 at 8192), with three 8192 (1200 x 1200: 56.2 and 53.7 there,
+    // 93.1 and 100.8 at 16384).  Half as many tiles need none below K = 4096 (300 x 3000 x 2048, 235 tiles: 27.2 us split, 13.2
+    // not; 500 x 1000 x 4096, 128 tiles, ties at 20.2; 128 x 4096 x 9216 23.6 and 41.8).
     const int64_t small = ((M + 63) / 64) * ((N + 63) / 64);
-    if (use && (small >= cus || (2 * small >= cus && K < 4096))) return 1;
+    if (use && small >= cus) {
+        const int64_t most = tiles * 4 <= cus ? (10 * M * N >= 9 * 4096 * small ? 4096 : 3584)
+                                              : (tiles * 3 < cus ? 6000 : 8192);
+        if (K <= most) return 1;
+    } else if (use && 2 * small >= cus && K < 4096) {
+        return 1;
+    }
     int64_t ks = (cus + tiles - 1) / tiles;
     if (ks > K / 256) ks = K / 256;
     if (ks > 16) ks = 16;

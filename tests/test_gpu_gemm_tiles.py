@@ -1,6 +1,7 @@
-"""Dense products on both sides of the rule that chooses their tiles, vs the oracle: 64 x 64 tiles
-up to two (three for K <= 1024) per compute unit, 128 x 128 beyond.  Int32 sums bit for bit, fp32
-outputs equal."""
+"""Dense products on both sides of the rules that choose tile and split, vs the oracle: 64 x 64 tiles
+up to two (three for K <= 1024) per compute unit, 128 x 128 beyond, and the reduction split or
+whole by K and the fill of the tiles.  Int32 sums bit for bit, fp32 outputs equal; a workspace of
+exactly the size the library asks for, its bytes past that untouched."""
 import numpy as np
 import pytest
 
@@ -45,3 +46,12 @@ def side(tiles, k):
 def test_tiles_per_cu(per, K, f, over):
     cus = torch_cuda().cuda.get_device_properties(0).multi_processor_count
     check(side(per * cus, 16) + (64 if over else 0), 1021, K, f, False, 500 + per)
+
+
+@pytest.mark.parametrize("M,N,K", [
+    (1000, 1000, 4096), (1000, 1000, 4112), (65, 8192, 3584), (65, 8192, 3600),    # four ranges, 64 tiles
+    (768, 1400, 6000), (768, 1400, 6016), (1200, 1200, 8192), (1200, 1200, 8208),  # four, three ranges
+    (500, 1000, 4080), (500, 1000, 4096)])                                        # 128 tiles of 64 x 64
+@pytest.mark.parametrize("f", [(4, 2), (3, 2)])
+def test_split_limits(M, N, K, f):
+    check(M, N, K, f, True, 520)
