@@ -472,8 +472,9 @@ hipError_t launch_mma(int op, int M, int N, int K, int groups, const ConvGeom& g
                       int64_t ldb, const Fmt& fb, const float* alphaB, int32_t* acc, float* y,
                       int64_t ldc, int32_t* part, hipStream_t s, const Post* post = nullptr);
 // Ranges of the reduction split for a dense GEMM of this shape (1: none), and
-// their length; use: for a contraction from codes (workspace sizes and packed
-// operands keep the split that a shape may have at most).
+// their length; use: for a contraction from codes.  Workspace sizes count the split that a
+// shape may have at most, so that a buffer made for a large product serves smaller ones,
+// which split more; packed operands keep that split.
 int mma_splitk(int64_t M, int64_t N, int64_t K, int* kchunk, bool use = false);
 
 // The same contraction (op 1 formats) with both operands first decoded once to

@@ -1371,8 +1371,9 @@ int mma_splitk(int64_t M, int64_t N, int64_t K, int* kchunk, bool use) {
     // 6144 26.1 and 29.8), 3584 where edges waste a tenth of the tiles (65 x 8192 x 4096
     // 19.8 and 21.5); with four ranges that overfill the chip 6000 (768 x 1400: 41.3 and 40.7
     // at 6144, 47.7 and 52.8 at 8192), with three 8192 (1200 x 1200: 56.2 and 53.7 there,
-    // 93.1 and 100.8 at 16384).  Half as many tiles need none below K = 4096 (300 x 3000 x 2048, 235 tiles: 27.2 us split, 13.2
-    // not; 500 x 1000 x 4096, 128 tiles, ties at 20.2; 128 x 4096 x 9216 23.6 and 41.8).
+    // 93.1 and 100.8 at 16384).  Half as many tiles need none below K = 4096 (300 x 3000 x
+    // 2048, 235 tiles: 27.2 us split, 13.2 not; 500 x 1000 x 4096, 128 tiles, ties at 20.2;
+    // 128 x 4096 x 9216 23.6 and 41.8).
     const int64_t small = ((M + 63) / 64) * ((N + 63) / 64);
     if (use && small >= cus) {
         const int64_t most = tiles * 4 <= cus ? (10 * M * N >= 9 * 4096 * small ? 4096 : 3584)
