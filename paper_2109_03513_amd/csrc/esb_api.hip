@@ -375,7 +375,7 @@ static int gemm_impl(int M, int N, int K, const uint8_t* A, int64_t lda, int nA,
     g.Nb = M; g.H = 1; g.W = 1; g.C = K; g.pitch = (int)(lda > 0x7fffffff ? 0x7fffffff : lda);
     g.Cg = K; g.R = 1; g.S = 1; g.sh = 1; g.sw = 1; g.ph = 0; g.pw = 0; g.P = 1; g.Q = 1;
     if (lda > 0x7fffffff) return ESB_E_INVALID;
-    if (b_layout == ESB_B_NK && pw_fits(g, M, N, 1, A, fa, B, ldb, fb, post && post->codes))
+    if (b_layout == ESB_B_NK && pw_fits(g, M, N, 1, A, fa, B, ldb, fb, acc, y, ldc, pp))
         return hip_status(launch_pw(g, M, N, A, fa, alphaA, B, ldb, fb, alphaB, acc, y, ldc,
                                     (hipStream_t)stream, pp));
     const int op = mma_choose(fa, fb, K);
@@ -475,7 +475,7 @@ static int conv_impl(const esb_conv_desc* d, const uint8_t* x, int nX, int kX_si
     const hipStream_t s = (hipStream_t)stream;
     if (conv_is_depthwise(d))
         return hip_status(launch_dwconv(g, x, fx, alphaX, w, fw, alphaW, acc, y, s, pp));
-    if (pw_fits(g, (int)Mrows, d->K, d->groups, x, fx, w, kred, fw, post && post->codes))
+    if (pw_fits(g, (int)Mrows, d->K, d->groups, x, fx, w, kred, fw, acc, y, d->K, pp))
         return hip_status(launch_pw(g, (int)Mrows, d->K, x, fx, alphaX, w, kred, fw, alphaW, acc, y,
                                     d->K, s, pp));
     const int op = mma_choose(fx, fw, kred);

@@ -543,10 +543,10 @@ hipError_t launch_stem(const ConvGeom& g, const uint8_t* x, const Fmt& fx, const
                        int QQ, const Post& post, hipStream_t s);
 
 // Contractions with a short reduction and many rows (1x1 convolutions without padding,
-// dense GEMMs, N x K filters with row pitch ldw), E4M3 in registers.  codes: the outputs
-// are codes.
+// dense GEMMs, N x K filters with row pitch ldw), E4M3 in registers.
 bool pw_fits(const ConvGeom& g, int M, int N, int groups, const uint8_t* x, const Fmt& fx,
-             const uint8_t* w, int64_t ldw, const Fmt& fw, bool codes);
+             const uint8_t* w, int64_t ldw, const Fmt& fw, const int32_t* acc, const float* y,
+             int64_t ldc, const Post* post);
 hipError_t launch_pw(const ConvGeom& g, int M, int N, const uint8_t* x, const Fmt& fx,
                      const float* alphaX, const uint8_t* w, int64_t ldw, const Fmt& fw,
                      const float* alphaW, int32_t* acc, float* y, int64_t ldc, hipStream_t s,

@@ -71,9 +71,11 @@ __device__ __forceinline__ void pw_load(const uint8_t* p, uint32_t* d) {
     }
 }
 
-// OUT 0: every epilogue; OUT 1: fp32 outputs without affine or int32 sums (residual, ReLU and
+// OUT 0: every epilogue; OUT 1: fp32 outputs without affine (residual, ReLU and
 // max|z| allowed), N and ldc multiples of 4, 16-byte aligned; OUT 2: codes without a residual
-// either, N and ldc multiples of 16.
+// either, N and ldc multiples of 16; OUT 3: int32 sums and perhaps plain fp32 outputs, aligned
+// as for OUT 1 (16-byte stores: by single words, 4 channels of 32 pixels a wave, they took
+// 1.5 to 4 times as long: 12544 x 1024 x 64 sums alone 41 us, here 16).
 template <int KS, int OUT, int V>
 __global__ __launch_bounds__(kPwThreads) void k_pw(PwParams p) {
     extern __shared__ __align__(16) uint8_t wl[];
@@ -208,7 +210,13 @@ __global__ __launch_bounds__(kPwThreads) void k_pw(PwParams p) {
 #pragma unroll
                     for (int e = 0; e < 4; e++) v[e] = s * ldexpf(a[4 * g + e], p.out_shift);
                     if (m >= p.M || cl >= ncur) continue;
-                    if (OUT == 1) {
+                    if (OUT == 3) {
+                        v4i n;
+#pragma unroll
+                        for (int e = 0; e < 4; e++) n[e] = (int32_t)ldexpf(a[4 * g + e], p.out_shift);
+                        *(v4i*)(p.acc + o) = n;
+                        if (p.y) *(f32x4*)(p.y + o) = v;
+                    } else if (OUT == 1) {
                         if (p.post.on) {
 #pragma unroll
                             for (int e = 0; e < 4; e++) {
@@ -245,7 +253,8 @@ template <int KS, int V>
 void launch_pw_t(const PwParams& p, int out, dim3 grid, size_t lds, hipStream_t s) {
     if (out == 0) k_pw<KS, 0, V><<<grid, kPwThreads, lds, s>>>(p);
     else if (out == 1) k_pw<KS, 1, V><<<grid, kPwThreads, lds, s>>>(p);
-    else k_pw<KS, 2, V><<<grid, kPwThreads, lds, s>>>(p);
+    else if (out == 2) k_pw<KS, 2, V><<<grid, kPwThreads, lds, s>>>(p);
+    else k_pw<KS, 3, V><<<grid, kPwThreads, lds, s>>>(p);
 }
 
 int pw_vec(const ConvGeom& g, const uint8_t* x, const uint8_t* w, int64_t ldw, int K) {
@@ -256,21 +265,83 @@ int pw_vec(const ConvGeom& g, const uint8_t* x, const uint8_t* w, int64_t ldw, i
     return 0;
 }
 
+// The instance for these outputs (OUT of k_pw).
+int pw_out(int N, const int32_t* acc, const float* y, int64_t ldc, const Post& P) {
+    const bool al4 = N % 4 == 0 && ldc % 4 == 0 && (uintptr_t)acc % 16 == 0 && (uintptr_t)y % 16 == 0 &&
+                     (uintptr_t)P.res % 16 == 0;
+    if (acc) return al4 && !P.on ? 3 : 0;
+    if (P.a || P.b) return 0;
+    if (y && !P.codes && al4) return 1;
+    if (!y && !P.res && P.codes && N % 16 == 0 && ldc % 16 == 0 && (uintptr_t)P.codes % 16 == 0) return 2;
+    return 0;
+}
+
+// Where the general instance (outputs in single words, post-processing per lane and channel)
+// beats the tiled and general kernels, measured over 5000 shapes and forms (us, there / here):
+// up to 16 channels, of which those pad a tile to 32 or 64 (64 -> 8 over 200704 rows, y
+// and codes 36 / 10); few bytes per row, which those load singly or half empty (24 -> 99 over
+// 200704 rows, codes 109 / 34); post-processing of channels in no multiple of four, which
+// those also store in single words; codes alone over many rows.  Against it: single-word y
+// or int32 stores in quantity (64 -> 1001 over 6272 rows, y, 11 / 26), and calls of a few
+// rows, where its epilogue's instruction fetches count (one row, 64 -> 64, affine and codes 4.6 / 6.0).
+bool pw_general(int M, int N, int K, const int32_t* acc, const float* y, const Post& P) {
+    const bool al = K % 16 == 0;                 // rows the tiled kernels take
+    const int64_t MN = (int64_t)M * N;
+    if (!P.on) {
+        if (N <= 16) return M >= 32 || !al;
+        return K < 16 && MN < (acc && y ? 50000 : 600000);
+    }
+    if (acc) return N <= 16;
+    if (M < 8) return K < 16 || N <= 8 || (!al && K >= 64 && N <= 16);
+    if (N < 32) return true;
+    if (P.codes && y) {
+        if (M >= 50000 && ((N <= 160 && N != 128 && !al) || (N <= 64 && N % 4))) return true;
+        if (K < 16) return MN < 3000000;
+        if (N % 4) return MN >= 2048 && MN < 5600000;
+        return N <= 44 && M >= 18000;
+    }
+    if (K < 16) return true;
+    if (N % 4) {
+        if (!y) return true;
+        if (N < 44 && al && K >= 128 && M < 50000) return false;   // half of 64 channels is padding
+        return N <= 256 || (P.res ? MN < 2000000 : K <= 224);
+    }
+    if (M >= 20000 && (K <= 224 || (N <= 64 && M >= 80000))) return true;
+    if (!al) return MN >= 3000000;
+    if (K <= 128 && N >= 512) return MN >= 6000000;
+    return (MN >= 25000000 && N >= 256) || (N <= 32 && M >= 45000);
+}
+
 }  // namespace
 
 bool pw_fits(const ConvGeom& g, int M, int N, int groups, const uint8_t* x, const Fmt& fx,
-             const uint8_t* w, int64_t ldw, const Fmt& fw, bool codes) {
+             const uint8_t* w, int64_t ldw, const Fmt& fw, const int32_t* acc, const float* y,
+             int64_t ldc, const Post* post) {
     const int K = g.Cg;
-    if (groups != 1 || g.R != 1 || g.S != 1 || g.ph != 0 || g.pw != 0 || K < 8 || K > 256) return false;
+    if (groups != 1 || g.R != 1 || g.S != 1 || g.ph != 0 || g.pw != 0 || K < 8 || K > 256 || N > 1024) return false;
     if (!mma_e4m3_ok(fx, fw, K) || pw_vec(g, x, w, ldw, K) == 0) return false;
-    // The tiled kernels stay for many fp32 outputs of more than 64 channels over aligned
+    const Post P = post ? *post : Post{};
+    const int out = pw_out(N, acc, y, ldc, P);
+    const int64_t MN = (int64_t)M * N;
+    if (out == 2) return true;
+    // The tiled kernels stay for many fp32 or int32 outputs of 65 to 512 channels over aligned
     // reductions of at least 64: their 128-channel rows leave in longer runs (64 -> 128 over
     // 50176 pixels 10.4 us there, 10.9 here, with a residual 15.2 against 16.4; 128 -> 256
-    // likewise 18.6 against 20.4; 192 -> 1024 over 12544 the other way, 23.7 against 19.1).
+    // likewise 18.6 against 20.4), and for more channels over the longest reductions, whose filter
+    // copies fill the LDS in several shares (256 -> 768 over 12544 pixels 17.8 against 22.2).
     // Few rows, few channels and codes are faster here (64 -> 64 over 200704 24.2 against 16.1,
     // codes 37.7 against 14.3; 64 -> 256 over 3136 5.1 against 4.2).
-    if (!codes && K % 16 == 0 && K >= 64 && N > 64 && N <= 512 && (int64_t)M * K >= 600000) return false;
-    return N <= 1024;
+    if (!P.codes && K % 16 == 0 && K >= 64 && (int64_t)M * K >= 600000) {
+        if (N > 64 && N <= 512) return false;
+        if (N > 512 && K > 192 && M < 20000 && MN >= 4000000 && MN < 15000000) return false;
+    }
+    if (out == 0) return pw_general(M, N, K, acc, y, P);
+    // Output rows 4 KB apart, 32 of which a store instruction meets, share few of the memory
+    // channels (8 -> 1024 over 50176 pixels 53 us there, 90 here); with the
+    // post-processing those kernels are slower too.
+    if (!P.on && ldc % 1024 == 0 && MN >= 19000000 && K <= 192) return false;
+    // Two output streams at once (64 -> 1024 over 12544 pixels 21.7 there, 34.1 here).
+    return !(out == 3 && y && N > 64 && MN >= 3000000);
 }
 
 hipError_t launch_pw(const ConvGeom& g, int M, int N, const uint8_t* x, const Fmt& fx,
@@ -290,15 +361,20 @@ hipError_t launch_pw(const ConvGeom& g, int M, int N, const uint8_t* x, const Fm
     p.kX = fx.k; p.kW = fw.k;
     const int V = pw_vec(g, x, w, ldw, p.K);
     const int KS = (p.K + 63) / 64;
-    p.tiles = (M + 31) / 32;
+    const int out = pw_out(N, acc, y, ldc, p.post);
+    p.tiles = (int)(((int64_t)M + 31) / 32);
     // channels per workgroup: even shares of whole 32-channel blocks that fit the LDS, and
     // more shares (each decodes the rows again) where one wave per tile leaves fewer than 8
     // waves per CU: 128 -> 256 channels over 12544 pixels, codes out, 22.3 us in one share,
     // 11.8 in six (with 16 waves per CU as the aim other shapes lose: 256 -> 256 over 12544
-    // 9.3 -> 12.7 us)
+    // 9.3 -> 12.7 us).  Up to 64 channels the number
+    // of shares is rounded: a second one for the last third of the 8 waves costs more than it
+    // gives (192 -> 64 over 65000 pixels 12.0 us in two, 9.4 in one); down for fp32 outputs over
+    // the longest rows (256 -> 64 over 43000 11.8 and 9.4).
     const int blocks32 = (N + 31) / 32, most = kPwLds / (32 * (64 * KS + 16));
     int ny = (blocks32 + most - 1) / most;
-    const int want = (8 * num_cus() + p.tiles - 1) / p.tiles;
+    const int up = N > 64 ? p.tiles - 1 : (KS == 4 && out != 2 ? 0 : p.tiles / 2);
+    const int want = (8 * num_cus() + up) / p.tiles;
     if (ny < want) ny = want < blocks32 ? want : blocks32;
     p.nch = 32 * ((blocks32 + ny - 1) / ny);
     const int gy = (N + p.nch - 1) / p.nch;
@@ -306,13 +382,6 @@ hipError_t launch_pw(const ConvGeom& g, int M, int N, const uint8_t* x, const Fm
     int64_t gx = (p.tiles + 3) / 4;
     const int64_t cap = ((int64_t)num_cus() * 4 + gy - 1) / gy;
     if (gx > cap) gx = cap;
-    const Post& P = p.post;
-    const bool lean = !acc && !P.a && !P.b;
-    int out = 0;
-    if (lean && y && !P.codes && N % 4 == 0 && ldc % 4 == 0 && (uintptr_t)y % 16 == 0 &&
-        (uintptr_t)P.res % 16 == 0)
-        out = 1;
-    if (lean && !y && !P.res && P.codes && N % 16 == 0 && ldc % 16 == 0 && (uintptr_t)P.codes % 16 == 0) out = 2;
     const dim3 grid((unsigned)gx, (unsigned)gy);
 #define ESB_PW(KSV) case KSV: if (V == 16) launch_pw_t<KSV, 16>(p, out, grid, lds, s); \
                               else launch_pw_t<KSV, 8>(p, out, grid, lds, s); break;

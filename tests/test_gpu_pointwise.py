@@ -99,3 +99,51 @@ def test_gemm_row_pitches(M, N, K, lda, ldb, ldc, off):
         assert (host(y)[:, N:] == -7.0).all()
     np.testing.assert_array_equal(host(acc)[:, :N], oacc)
     assert (host(acc)[:, N:] == -7).all()
+
+
+# M, N, K on both sides of the lines between this kernel and the tiled and general ones
+ROUTES = [
+    (7, 24, 64), (8, 24, 64), (7, 8, 64), (5, 16, 200), (40, 31, 48), (40, 32, 48), (31, 9, 64), (33, 9, 64),
+    (2344, 65, 256), (2343, 65, 256), (100, 40, 8), (3000, 200, 8), (3001, 200, 8), (700, 33, 128),
+    (20000, 36, 64), (19999, 36, 64), (46000, 32, 256), (1200, 1000, 96), (1203, 1001, 200)]
+
+
+@pytest.mark.parametrize("M,N,K", ROUTES)
+@pytest.mark.parametrize("form", ["sums", "acc", "affine_codes", "affine_all", "residual", "codes", "sums_all"])
+def test_routes(M, N, K, form):
+    from paper_2109_03513_amd import esb
+    A = wl.random_codes(98, (M, K), 8)
+    B = wl.random_codes(99, (N, K), 8)
+    rows = np.unique(np.concatenate([np.arange(0, M, max(1, M // 300)), np.arange(max(0, M - 33), M)]))
+    st, oacc, oy = oracle.gemm(np.ascontiguousarray(A[rows]), B, 5, 3, 0.37, 5, 3, 0.021)
+    assert st == 0
+    log("routes %s %s" % ((M, N, K), form))
+    head = (dev(A), 5, 3, scalar(0.37), dev(B), 5, 3, scalar(0.021))
+    if form in ("sums", "acc"):
+        acc, y = esb.esb_gemm(*head, want_y=form == "sums")
+        np.testing.assert_array_equal(host(acc)[rows], oacc)
+        if y is not None:
+            np.testing.assert_array_equal(host(y)[rows], oy)
+        return
+    r = np.random.default_rng([98, N, K])
+    sd = float(np.std(oy)) or 1.0
+    qa = np.float32(0.4 * sd)
+    a = b = res = None
+    if form != "codes":
+        a = r.uniform(-0.5, 1.5, N).astype(np.float32)
+        b = (r.standard_normal(N) * 0.3 * sd).astype(np.float32)
+    if form == "residual":
+        a = b = None
+        res = (r.standard_normal((M, N)) * sd).astype(np.float32)
+    codes_only, y_only = form in ("codes", "affine_codes"), form == "residual"
+    oz, oc = oracle.post(oy, 5, 3, qa, a=a, bias=b, res=None if res is None else res[rows], relu=True)
+    acc, y, codes = esb.esb_gemm_post(
+        *head, scalar(qa), 5, 3, a=None if a is None else dev(a), b=None if b is None else dev(b),
+        residual=None if res is None else dev(res), relu=True, want_codes=not y_only,
+        want_y=not codes_only, want_acc=form == "sums_all")
+    if acc is not None:
+        np.testing.assert_array_equal(host(acc)[rows], oacc)
+    if y is not None:
+        np.testing.assert_array_equal(host(y)[rows].view(np.uint32), oz.view(np.uint32))
+    if codes is not None:
+        np.testing.assert_array_equal(host(codes)[rows], oc)
