@@ -8,7 +8,7 @@ import numpy as np
 import pytest
 
 import oracle
-from gpuutil import dev, host, log, scalar
+from gpuutil import dev, host, log, scalar, torch_cuda
 from paper_2109_03513_amd import workloads as wl
 
 pytestmark = pytest.mark.gpu
@@ -23,7 +23,8 @@ CONVS = [
     (2, 11, 8, 144, 24, 1, (5, 3), (5, 3)),
     (1, 8, 8, 200, 100, 2, (6, 4), (5, 2)),
     (1, 5, 7, 256, 1024, 1, (5, 3), (5, 3)),
-    (70, 30, 30, 16, 32, 1, (5, 3), (5, 3)),     # more tiles than waves
+    (70, 30, 30, 16, 32, 1, (5, 3), (5, 3)),     # one tile for most waves, none for some
+    (1, 40, 40, 24, 24, 1, (5, 3), (5, 3)),
 ]
 
 
@@ -99,6 +100,49 @@ def test_gemm_row_pitches(M, N, K, lda, ldb, ldc, off):
         assert (host(y)[:, N:] == -7.0).all()
     np.testing.assert_array_equal(host(acc)[:, :N], oacc)
     assert (host(acc)[:, N:] == -7).all()
+
+
+def rows_per_wave(gy):
+    """Rows that give every wave of a launch with gy channel shares one tile."""
+    return 32 * 4 * -(-4 * torch_cuda().cuda.get_device_properties(0).multi_processor_count // gy)
+
+
+@pytest.mark.parametrize("N,K,gy", [(32, 16, 1), (1024, 256, 5)])
+@pytest.mark.parametrize("form", ["sums", "y", "residual", "codes"])
+def test_several_tiles_per_wave(N, K, gy, form):
+    """More than twice as many tiles as waves, the last one ragged: the next tile's codes and
+    residual are fetched while this one is computed, the maximum runs over all tiles."""
+    from paper_2109_03513_amd import esb
+    M = 2 * rows_per_wave(gy) + 32 * 5 + 7
+    A = wl.random_codes(96, (M, K), 8)
+    B = wl.random_codes(97, (N, K), 8)
+    step = 1 if M * N * K < 2 ** 28 else 97
+    rows = np.unique(np.concatenate([np.arange(0, M, step), np.arange(M - 40, M)]))
+    st, oacc, oy = oracle.gemm(np.ascontiguousarray(A[rows]), B, 5, 3, 0.37, 5, 3, 0.021)
+    assert st == 0
+    log("several tiles per wave %s %s" % ((M, N, K), form))
+    head = (dev(A), 5, 3, scalar(0.37), dev(B), 5, 3, scalar(0.021))
+    if form in ("sums", "y"):
+        acc, y = esb.esb_gemm(*head, want_acc=form == "sums")
+        if form == "sums":
+            np.testing.assert_array_equal(host(acc)[rows], oacc)
+        np.testing.assert_array_equal(host(y)[rows], oy)
+        return
+    sd = float(np.std(oy))
+    qa = np.float32(0.4 * sd)
+    torch = torch_cuda()
+    res = torch.randn(M, N, device="cuda", generator=torch.Generator("cuda").manual_seed(3)) * sd
+    ores = host(res)[rows] if form == "residual" else None
+    oz, oc = oracle.post(oy, 5, 3, qa, res=ores, relu=form == "codes")
+    amax = scalar(0.0)
+    _, y, codes = esb.esb_gemm_post(*head, scalar(qa), 5, 3, residual=res if form == "residual" else None,
+                                    relu=form == "codes", want_codes=form == "codes",
+                                    want_y=form == "residual", absmax=amax)
+    if form == "codes":
+        np.testing.assert_array_equal(host(codes)[rows], oc)
+        _, y, _ = esb.esb_gemm_post(*head, scalar(qa), 5, 3, relu=True, want_codes=False, want_y=True)
+    np.testing.assert_array_equal(host(y)[rows].view(np.uint32), oz.view(np.uint32))
+    assert host(amax)[0] == np.abs(host(y)).max()
 
 
 # M, N, K on both sides of the lines between this kernel and the tiled and general ones
