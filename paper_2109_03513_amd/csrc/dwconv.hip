@@ -343,6 +343,13 @@ __global__ __launch_bounds__(kDwThreads) void k_dw3(Dw3Params p) {
     if (p.post.on) post_absmax_flush(p.post, amax);
 }
 
+// OUT of k_dw3 for these outputs.
+static int dw3_out(const ConvGeom& g, const int32_t* acc, const float* y, const Post& P) {
+    const bool lean = g.Q >= 4 && !acc && !P.a && !P.b && !P.res && (y != nullptr) != (P.codes != nullptr) &&
+                      (uintptr_t)P.codes % 4 == 0;
+    return !lean ? 0 : (y ? 1 : 2);
+}
+
 template <int MODE>
 static void launch_dw3_mode(const Dw3Params& p, int out, int blocks, hipStream_t s) {
     if (out == 0) k_dw3<0, MODE><<<blocks, kDwThreads, 0, s>>>(p);
@@ -371,10 +378,7 @@ static hipError_t launch_dw3(const ConvGeom& g, const uint8_t* x, const Fmt& fx,
     p.strips = (g.P + p.rows - 1) / p.rows;
     p.total = (int)(per_row * p.strips);   // <= 2^30 + per_row: see dw3_fits
     const int blocks = (p.total + kDwThreads - 1) / kDwThreads;
-    const Post& P = p.post;
-    const bool lean = g.Q >= 4 && !acc && !P.a && !P.b && !P.res && (y != nullptr) != (P.codes != nullptr) &&
-                      (uintptr_t)P.codes % 4 == 0;
-    const int out = !lean ? 0 : (y ? 1 : 2);
+    const int out = dw3_out(g, acc, y, p.post);
     if (p.dx.mode == 3) launch_dw3_mode<3>(p, out, blocks, s);
     else if (p.dx.mode == 4) launch_dw3_mode<4>(p, out, blocks, s);
     else launch_dw3_mode<5>(p, out, blocks, s);
@@ -383,10 +387,31 @@ static hipError_t launch_dw3(const ConvGeom& g, const uint8_t* x, const Fmt& fx,
 
 // The conditions of k_dw3: its byte permutes decode activations of at most five bits
 // (longer formats would decode arithmetically, more work than the table kernels), and its
-// dword loads and 16-byte stores need aligned tensors.
+// dword loads and 16-byte stores need aligned tensors.  It walks a strip of rows per thread, a
+// longer chain than one output's, and its general epilogue (OUT 0) is four times the code, while the
+// other kernels copy the filter through LDS per workgroup: small calls with few channels are
+// faster there.  Measured over 3800 shapes and forms (us, k_dwconv16 or k_dwconv / here):
+//  * C % 16 == 0: the lean outputs and int32 sums are faster here at every size (16 channels
+//    6.3 / 5.3, 960 10.4 / 4.5), the general ones from 64 channels on, 192 with an affine (affine
+//    and codes at 14 x 14: 32 channels 8.1 / 9.4, 192 9.6 / 9.6, 960 14.2 / 9.4), or over 2^20 outputs;
+//  * else: lean outputs with ReLU or max|z| (5.8 / 5.4), y from 16 channels, codes and sums
+//    from 64, or over 2^18 (sums 2^19) outputs; other epilogues over 2^20 (affine and codes at 2^15
+//    6.8 / 10.1, at 2^20 11.3 / 10.0);
+//  * fewer than four columns, whole threads of padding: C % 16 == 0 alone, codes of single pixels,
+//    else 48 channels and more, 144 without post-processing or over 2048 outputs.
 static bool dw3_fits(const ConvGeom& g, const uint8_t* x, const Fmt& fx, const Fmt& fw,
-                     const int32_t* acc, const float* y) {
-    return g.R == 3 && g.S == 3 && g.sh == 1 && g.sw == 1 && g.C % 4 == 0 && fx.n <= 5 &&
+                     const int32_t* acc, const float* y, const Post* post) {
+    const Post P = post ? *post : Post{};
+    const bool c16 = g.C % 16 == 0, affine = P.a || P.b;
+    const int64_t outputs = (int64_t)g.Nb * g.P * g.Q * g.C;
+    bool pays;
+    if (dw3_out(g, acc, y, P)) pays = c16 || (P.on && y) || g.C >= (y ? 16 : 64) || outputs >= 1 << 18;
+    else if (g.Q < 4 && !c16) pays = outputs >= 1 << 20;
+    else if (g.Q == 1) pays = P.codes || (outputs < 300000 && (P.on || g.C >= 144));
+    else if (g.Q < 4) pays = P.on ? g.C >= 48 : (g.C >= 144 || outputs >= 2048);
+    else if (!P.on) pays = c16 || g.C >= 64 || outputs >= 1 << 19;
+    else pays = (c16 && g.C >= (affine ? 192 : 64)) || outputs >= 1 << 20;
+    return pays && g.R == 3 && g.S == 3 && g.sh == 1 && g.sw == 1 && g.C % 4 == 0 && fx.n <= 5 &&
            fx.max_int <= 127 && fw.max_int <= 127 && (uintptr_t)x % 4 == 0 &&
            (!acc || (uintptr_t)acc % 16 == 0) && (!y || (uintptr_t)y % 16 == 0) &&
            (int64_t)g.Nb * g.P * ((g.Q + 3) / 4) * (g.C / 4) < ((int64_t)1 << 30) &&
@@ -396,7 +421,7 @@ static bool dw3_fits(const ConvGeom& g, const uint8_t* x, const Fmt& fx, const F
 hipError_t launch_dwconv(const ConvGeom& g, const uint8_t* x, const Fmt& fx, const float* alphaX,
                          const uint8_t* w, const Fmt& fw, const float* alphaW, int32_t* acc,
                          float* y, hipStream_t s, const Post* post) {
-    if (dw3_fits(g, x, fx, fw, acc, y))
+    if (dw3_fits(g, x, fx, fw, acc, y, post))
         return launch_dw3(g, x, fx, alphaX, w, fw, alphaW, acc, y, s, post);
     DwParams p;
     p.g = g; p.x = x; p.w = w; p.alphaX = alphaX; p.alphaW = alphaW; p.acc = acc; p.y = y;
