@@ -52,6 +52,8 @@ constexpr int kMaxCols = kThreads / 4;  // Q + 2: one thread per 16-byte chunk o
 constexpr int SLAB = 72;                // fp32 row stride of the epilogue slabs
 constexpr int kMaxFill = 10;            // patch chunks per thread and chunk of channels
 constexpr int kFewFill = 5;             // the same where this many suffice
+constexpr int kMidFill = 9;             // likewise (several chunks, 128-pixel tiles), and
+constexpr int kSumsFill = 8;            // with int32 sums: each one more spills there
 constexpr int kWPer = NT * TAPS * 4 / kThreads;   // filter chunks per thread (9)
 static_assert(4 * 32 * SLAB * 4 <= kPatchMax, "epilogue slabs fit the patch");
 static_assert(kWPer * kThreads == NT * TAPS * 4, "whole filter chunks per thread");
@@ -1047,7 +1049,8 @@ hipError_t launch_conv3x3(const ConvGeom& g, int K, const uint8_t* x, const Fmt&
     p.ntm = (p.M + 32 * tmb - 1) / (32 * tmb);
     // patch chunks per thread: 5 where they suffice (all but wide images), else kMaxFill
     const int rstep = kThreads / (4 * (g.W + 2));
-    const bool few = (patch_rows_max(g.P, g.Q, 32 * tmb, g.H, p.st) + rstep - 1) / rstep <= kFewFill;
+    const int fill = (patch_rows_max(g.P, g.Q, 32 * tmb, g.H, p.st) + rstep - 1) / rstep;
+    const bool few = fill <= kFewFill;
     // the reduction in two halves (see k_conv3x3): one tile per CU at most, six chunks or more
     if (!acc && g.C >= 6 * CK && (int64_t)p.ntm * p.ntn <= num_cus()) {
         const unsigned blocks = (unsigned)(p.ntm * p.ntn);
@@ -1064,6 +1067,11 @@ hipError_t launch_conv3x3(const ConvGeom& g, int K, const uint8_t* x, const Fmt&
 #undef ESB_CONV3_LAUNCH
         return hipGetLastError();
     }
+    // Wide images, whose tiles of 128 pixels take more than five patch chunks per thread, have no
+    // registers for the residual beside those of the next chunk: 128 -> 384 at 60 x 60, batch 4,
+    // 33.0 us straight from the accumulators with room for ten chunks (48 registers spilled), 27.6
+    // through the slabs with room for nine (12 spilled).
+    if (multi && tmb == 4 && !few && p.post.res) p.direct = 0;
     // persistent workgroups, a whole number per channel tile, two per CU
     int per = (num_cus() * 2) / p.ntn;
     if (per < 1) per = 1;
@@ -1086,6 +1094,9 @@ hipError_t launch_conv3x3(const ConvGeom& g, int K, const uint8_t* x, const Fmt&
     if (!multi && tmb == 8) ESB_CONV3_LAUNCH(8, false);
     else if (!multi && tmb == 4) ESB_CONV3_LAUNCH(4, false);
     else if (!multi) ESB_CONV3_LAUNCH(2, false);
+    else if (tmb == 4 && acc && !few && fill <= kSumsFill)
+        k_conv3x3<4, true, 3, kSumsFill><<<blocks, kThreads, 0, s>>>(p);
+    else if (tmb == 4 && !few && fill <= kMidFill) ESB_CONV3_LAUNCH2(4, true, kMidFill);
     else if (tmb == 4) ESB_CONV3_LAUNCH(4, true);
     else ESB_CONV3_LAUNCH(2, true);
 #undef ESB_CONV3_LAUNCH

@@ -165,6 +165,38 @@ def test_conv3x3_direct_random_shapes(esb, st, Nb, H, W, C, K):
     np.testing.assert_array_equal(host(y).view(np.uint32), y_o.view(np.uint32))
 
 
+def check_images(esb, Nb, H, W, C, K, form, images, seed):
+    """One form of a stride-1 layer on Nb images, the listed ones against the oracle: bit-exact
+    sums, outputs and codes, and the maximum of all outputs."""
+    x = wl.random_codes(seed, (Nb, H, W, C), 5)
+    w = wl.random_codes(seed + 1, (K, 3, 3, C), 5)
+    status, acc_o, y_o = oracle.conv2d(np.ascontiguousarray(x[images]), w, 5, 3, ALPHA_X, 5, 3, ALPHA_W,
+                                       pad=(1, 1))
+    assert status == 0
+    log("conv3x3 images %s %s" % ((Nb, H, W, C, K), form))
+    head = (dev(x), 5, 3, scalar(ALPHA_X), dev(w), 5, 3, scalar(ALPHA_W))
+    if form in ("plain", "sums"):
+        acc, y = esb.esb_conv2d(*head, pad=(1, 1), want_acc=form == "sums")
+        if form == "sums":
+            np.testing.assert_array_equal(host(acc)[images], acc_o)
+        np.testing.assert_array_equal(host(y)[images].view(np.uint32), y_o.view(np.uint32))
+        return
+    a, b, res, _, qa = post_params(13, np.broadcast_to(y_o[:1], (Nb,) + y_o.shape[1:]), K,
+                                   {"affine": "affine", "all": "all", "residual": "residual"}.get(form, "none"))
+    z_o, codes_o = oracle.post(y_o.reshape(-1, K), 5, 3, qa, a=a, bias=b, relu=True,
+                               res=None if res is None else res[images].reshape(-1, K))
+    amax = scalar(0.0)
+    _, y, codes = esb.esb_conv2d_post(
+        *head, scalar(qa), 5, 3, a=None if a is None else dev(a), b=None if b is None else dev(b),
+        residual=None if res is None else dev(res), relu=True, pad=(1, 1),
+        want_codes=form in ("codes", "y_codes", "all"), want_y=form != "codes", absmax=amax)
+    if y is not None:
+        np.testing.assert_array_equal(host(y)[images].reshape(-1, K).view(np.uint32), z_o.view(np.uint32))
+        assert host(amax)[0] == np.abs(host(y)).max()
+    if codes is not None:
+        np.testing.assert_array_equal(host(codes)[images].reshape(-1, K), codes_o)
+
+
 # stride, N, H, W, C, K
 HALVED = [
     (1, 1, 7, 7, 384, 64),       # six chunks: three per half; one 64-pixel tile
@@ -246,3 +278,13 @@ def test_conv3x3_direct_outputs(esb, st, Nb, H, W, C, K, form):
     elif form != "absmax":
         np.testing.assert_array_equal(host(y).reshape(-1, K).view(np.uint32), z_o.view(np.uint32))
     assert host(amax)[0] == np.max(np.abs(z_o))
+
+
+# several chunks, 128-pixel tiles, eight, nine and ten patch chunks per thread: N, H, W, C, K
+WIDE = [(2, 56, 56, 128, 256), (4, 40, 40, 192, 192), (7, 31, 31, 128, 256), (3, 57, 47, 256, 192)]
+
+
+@pytest.mark.parametrize("Nb,H,W,C,K", WIDE)
+@pytest.mark.parametrize("form", ["plain", "sums", "residual", "codes", "all"])
+def test_conv3x3_wide_images(esb, Nb, H, W, C, K, form):
+    check_images(esb, Nb, H, W, C, K, form, sorted({0, Nb // 2, Nb - 1}), 9000 + W)
