@@ -358,7 +358,7 @@ void k_conv3x3(Conv3Params p) {
     constexpr int NMB = TMB >= 8 ? 2 : 1;    // output blocks of a wave: NMB x NNB
     constexpr int NNB = TMB >= 4 ? 2 : 1;
     static_assert(4 * NMB * NNB == 2 * TMB, "four waves cover the tile");
-    static_assert(!MULTI || TMB <= 4 || KG == 2, "several chunks: at most 4 pixel blocks");
+    static_assert(!MULTI || TMB <= 4, "several chunks: at most 4 pixel blocks");
     constexpr bool ACC = OUT == 3;
     static_assert(KG == 1 || (MULTI && !ACC), "halves of the reduction: several chunks");
     __shared__ __align__(16) uint8_t wlds_all[KG][NT * WST];
@@ -605,42 +605,29 @@ void k_conv3x3(Conv3Params p) {
             amax = max(amax, store_block<32, true>(p, slab, SLAB, m0 + 32 * mbw, n0 + 32 * nbw, lane, qa));
             continue;
         } else if constexpr (KG == 2) {
-            // each half gives away what the other stores (two pixel blocks per wave: one of
-            // them, else one of the two channel blocks) and adds what it gets
-            constexpr int NX = NMB == 2 ? 2 : 1;             // 32 x 32 blocks given away
-            static_assert(NX * 16 * kThreads * 4 <= kPatchMax, "the blocks fit the patch");
+            // each half gives the other one of its two channel blocks, adds what it gets to the
+            // block of its own number and stores that
+            static_assert(16 * kThreads * 4 <= kPatchMax, "a block of every wave fits the patch");
             float* out = (float*)patch_all[half ^ 1];
             const float* in = (const float*)patch;
 #pragma unroll
-            for (int x = 0; x < NX; x++) {
-                const v16f v0 = NMB == 2 ? acc[0][x] : acc[0][0], v1 = NMB == 2 ? acc[NMB - 1][x] : acc[0][1];
-#pragma unroll
-                for (int r = 0; r < 16; r++)
-                    out[(x * 16 + r) * kThreads + tid] = half ? v0[r] : v1[r];
-            }
+            for (int r = 0; r < 16; r++) out[r * kThreads + tid] = half ? acc[0][0][r] : acc[0][1][r];
             __syncthreads();
-            v16f sum[NX];
+            v16f sum[1];
 #pragma unroll
-            for (int x = 0; x < NX; x++) {
-                const v16f v0 = NMB == 2 ? acc[0][x] : acc[0][0], v1 = NMB == 2 ? acc[NMB - 1][x] : acc[0][1];
-#pragma unroll
-                for (int r = 0; r < 16; r++)
-                    sum[x][r] = (half ? v1[r] : v0[r]) + in[(x * 16 + r) * kThreads + tid];
-            }
-            constexpr int WC = 32 * NX;
-            const int mrow = m0 + 32 * (mbw + (NMB == 2 ? half : 0)), cc = NMB == 2 ? 0 : 32 * half;
+            for (int r = 0; r < 16; r++) sum[0][r] = (half ? acc[0][1][r] : acc[0][0][r]) + in[r * kThreads + tid];
+            const int mrow = m0 + 32 * mbw, cc = 32 * half;
             if constexpr (OUT == 1 || OUT == 2) {
-                f32x4 res[4 * NX];
-                if (OUT == 1 && p.post.res) load_res<NX>(p, res, mrow, n0 + cc, lane);
-                amax = max(amax, store_direct<NX, OUT>(p, sum, res, mrow, n0 + cc, lane, s, qa));
+                f32x4 res[4];
+                if (OUT == 1 && p.post.res) load_res<1>(p, res, mrow, n0 + cc, lane);
+                amax = max(amax, store_direct<1, OUT>(p, sum, res, mrow, n0 + cc, lane, s, qa));
                 continue;
             }
             __syncthreads();
             float* slab = (float*)patch + wave * (32 * SLAB);
-#pragma unroll
-            for (int x = 0; x < NX; x++) to_slab(slab, SLAB, sum[x], 32 * x, lane, s, p.out_shift);
+            to_slab(slab, SLAB, sum[0], 0, lane, s, p.out_shift);
             __syncthreads();
-            amax = max(amax, store_block<WC, true>(p, slab, SLAB, mrow, n0 + cc, lane, qa));
+            amax = max(amax, store_block<32, true>(p, slab, SLAB, mrow, n0 + cc, lane, qa));
             continue;
         }
         float* slab = (float*)patch + wave * (32 * SLAB);
@@ -1091,7 +1078,7 @@ hipError_t launch_conv3x3(const ConvGeom& g, int K, const uint8_t* x, const Fmt&
         if (few) ESB_CONV3_LAUNCH2(TMB, MULTI, kFewFill);                            \
         else ESB_CONV3_LAUNCH2(TMB, MULTI, kMaxFill);                                \
     } while (0)
-    if (!multi && tmb == 8) ESB_CONV3_LAUNCH(8, false);
+    if (!multi && tmb == 8) ESB_CONV3_LAUNCH2(8, false, kMaxFill);   // its tiles have six rows of chunks and more
     else if (!multi && tmb == 4) ESB_CONV3_LAUNCH(4, false);
     else if (!multi) ESB_CONV3_LAUNCH(2, false);
     else if (tmb == 4 && acc && !few && fill <= kSumsFill)
