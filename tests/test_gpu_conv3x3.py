@@ -288,3 +288,34 @@ WIDE = [(2, 56, 56, 128, 256), (4, 40, 40, 192, 192), (7, 31, 31, 128, 256), (3,
 @pytest.mark.parametrize("form", ["plain", "sums", "residual", "codes", "all"])
 def test_conv3x3_wide_images(esb, Nb, H, W, C, K, form):
     check_images(esb, Nb, H, W, C, K, form, sorted({0, Nb // 2, Nb - 1}), 9000 + W)
+
+
+@pytest.mark.parametrize("st,Nb,H,C,K", [(1, 5400, 56, 256, 64), (2, 45000, 14, 512, 64)])
+def test_conv3x3_inputs_past_4_gib(esb, st, Nb, H, C, K):
+    """Inputs of more than 2^32 bytes run in parts of whole images: images on both sides of the
+    seam, the first and the last against the oracle, the residual and output of each at its place,
+    one maximum over all."""
+    torch = torch_cuda()
+    assert Nb * H * H * C > 2 ** 32
+    gen = torch.Generator("cuda").manual_seed(5)
+    x = torch.randint(0, 32, (Nb, H, H, C), dtype=torch.uint8, device="cuda", generator=gen)
+    w = wl.random_codes(9100, (K, 3, 3, C), 5)
+    images = [0, Nb // 2 - 1, Nb // 2, Nb - 1]
+    status, _, y_o = oracle.conv2d(host(x[images]), w, 5, 3, ALPHA_X, 5, 3, ALPHA_W, stride=(st, st), pad=(1, 1))
+    assert status == 0
+    sd = float(np.std(y_o))
+    qa = np.float32(0.4 * sd)
+    P = y_o.shape[1]
+    log("conv3x3 past 4 GiB stride %d %s" % (st, (Nb, H, C, K)))
+    head = (x, 5, 3, scalar(ALPHA_X), dev(w), 5, 3, scalar(ALPHA_W))
+    y = torch.randn((Nb, P, P, K), device="cuda", generator=gen) * sd     # the residual, replaced
+    res = host(y[images])
+    z_o, _ = oracle.post(y_o.reshape(-1, K), 5, 3, qa, res=res.reshape(-1, K), relu=True)
+    amax = scalar(0.0)
+    esb.esb_conv2d_post(*head, scalar(qa), 5, 3, residual=y, y=y, relu=True, stride=(st, st), pad=(1, 1),
+                        want_codes=False, absmax=amax)
+    np.testing.assert_array_equal(host(y[images]).reshape(-1, K).view(np.uint32), z_o.view(np.uint32))
+    assert host(amax)[0] == float(y.abs().max())
+    _, codes_o = oracle.post(y_o.reshape(-1, K), 5, 3, qa, relu=True)
+    _, _, codes = esb.esb_conv2d_post(*head, scalar(qa), 5, 3, relu=True, stride=(st, st), pad=(1, 1))
+    np.testing.assert_array_equal(host(codes[images]).reshape(-1, K), codes_o)
