@@ -899,8 +899,10 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_mma_pre(FastParams g) {
 // so that a stage lies inside one filter tap (r, s): every lane of a stage
 // then shares (r, s, channel block).  MFMA: 32x32x64 with
 // cbsz = blgp = 2 (E2M3), six operand VGPRs; the MFMAs of a stage come in two
-// parts around the barrier as in k_mma_pre.
-template <int BM, int BN, int WGM, int WGN, int CONV, int R>
+// parts around the barrier as in k_mma_pre.  POST: the fused post-processing, an instance of its
+// own: inlined behind a branch it costs the main loop of plain calls registers and moves (8192^3
+// in ESB(5,2) 623 us with it, 466 without, 2.36 POPS; 4097 x 4100 x 1024 63.2 and 55.3).
+template <int BM, int BN, int WGM, int WGN, int CONV, int R, bool POST>
 __global__ __launch_bounds__(64 * WGM * WGN) void k_mma_f6(FastParams g) {
     constexpr int NW = WGM * WGN;
     constexpr int WM = BM / WGM, WN = BN / WGN;
@@ -1060,8 +1062,8 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_mma_f6(FastParams g) {
     vm_wait<0>();   // the fetches past the end (+0 rows) land before the workgroup ends
 
     float s = 0.0f;
-    if (g.y || g.post.on) s = ldexpf(g.alphaA[0] * g.alphaB[0], -(g.kA + g.kB));
-    if (g.post.on && (CONV || g.ksplit == 1)) {
+    if (g.y || POST) s = ldexpf(g.alphaA[0] * g.alphaB[0], -(g.kA + g.kB));
+    if constexpr (POST) {
         static_assert(NW * 32 * 32 * TJ * 4 <= R * TILE, "post slabs fit the ring");
         if (g.acc)
             store_acc<TI, TJ>(g, lane, m0 + wr, n0 + wc, grp, [&](int i, int j, int r) {
@@ -1095,8 +1097,10 @@ hipError_t launch_f6_t(FastParams g, int groups, bool conv, hipStream_t s) {
     g.ntiles = g.tiles_m * g.tiles_n;
     dim3 grid(g.ntiles, 1, groups);
     const int nt = 64 * WGM * WGN;
-    if (conv) k_mma_f6<BM, BN, WGM, WGN, 1, R><<<grid, nt, 0, s>>>(g);
-    else k_mma_f6<BM, BN, WGM, WGN, 0, R><<<grid, nt, 0, s>>>(g);
+    if (conv && g.post.on) k_mma_f6<BM, BN, WGM, WGN, 1, R, true><<<grid, nt, 0, s>>>(g);
+    else if (conv) k_mma_f6<BM, BN, WGM, WGN, 1, R, false><<<grid, nt, 0, s>>>(g);
+    else if (g.post.on) k_mma_f6<BM, BN, WGM, WGN, 0, R, true><<<grid, nt, 0, s>>>(g);
+    else k_mma_f6<BM, BN, WGM, WGN, 0, R, false><<<grid, nt, 0, s>>>(g);
     return hipGetLastError();
 }
 
