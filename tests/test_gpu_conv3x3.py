@@ -36,7 +36,7 @@ def unaligned(torch, a):
 CASES = [
     # N, H, W, C, K, fx, fw, variant
     (2, 56, 56, 64, 64, (5, 3), (5, 3), "plain"),     # the ResNet18 l1 shape, batch 2
-    (3, 7, 7, 64, 64, (5, 3), (5, 3), "all"),         # 49-pixel images: a tile spans six of them
+    (3, 7, 7, 64, 64, (5, 3), (5, 3), "all"),         # 49-pixel images: 64-pixel tiles over two
     (1, 13, 5, 64, 64, (4, 2), (5, 3), "relu"),       # H != W, ragged last tile, mixed formats
     (2, 9, 62, 64, 64, (5, 3), (4, 2), "residual"),   # widest rows taken (Q + 2 = 64)
     (1, 1, 1, 64, 64, (5, 3), (5, 3), "affine"),      # one pixel
@@ -46,8 +46,9 @@ CASES = [
     (3, 14, 14, 256, 192, (5, 3), (4, 2), "relu"),    # four chunks, three channel tiles
     (1, 5, 9, 192, 64, (5, 3), (5, 3), "residual"),   # three chunks, ragged
     (2, 7, 7, 512, 128, (5, 3), (5, 3), "plain"),     # eight chunks (the l4 reduction)
-    # one chunk: 64-pixel tiles when tiles of 128 give fewer workgroups than CUs; several
-    # chunks: 128-pixel tiles down to half a workgroup per CU
+    # one chunk (all of this list): 64-pixel tiles, for tiles of 128 give fewer workgroups than
+    # CUs (the larger tiles: test_conv3x3_one_chunk); several chunks: 128-pixel tiles down to
+    # half a workgroup per CU
     (50, 7, 7, 128, 512, (5, 3), (5, 3), "plain"),    # several chunks, 128-pixel tiles
     (16, 14, 14, 64, 512, (5, 3), (5, 3), "affine"),  # one chunk, eight channel tiles
     (8, 1, 40, 128, 64, (5, 3), (5, 3), "all"),       # several chunks, 64-pixel tiles (one-row
@@ -288,6 +289,36 @@ WIDE = [(2, 56, 56, 128, 256), (4, 40, 40, 192, 192), (7, 31, 31, 128, 256), (3,
 @pytest.mark.parametrize("form", ["plain", "sums", "residual", "codes", "all"])
 def test_conv3x3_wide_images(esb, Nb, H, W, C, K, form):
     check_images(esb, Nb, H, W, C, K, form, sorted({0, Nb // 2, Nb - 1}), 9000 + W)
+
+
+# one chunk: pixels per tile, patch chunks per thread the kernel is built for, H, W, K
+ONE_CHUNK = [
+    (256, 10, 56, 56, 64),     # the ResNet18 l1 shape: ten patch rows, one per step
+    (256, 10, 7, 7, 512),      # tiles over seven images
+    (256, 10, 31, 23, 128),    # ragged last tile
+    (128, 5, 28, 28, 64),
+    (128, 5, 13, 13, 192),     # ragged last tile
+    (128, 5, 7, 7, 256),       # tiles over four images
+    (128, 10, 56, 56, 64),
+    (128, 10, 29, 25, 128),    # ragged last tile
+]
+
+
+@pytest.mark.parametrize("tile,fill,H,W,K", ONE_CHUNK)
+@pytest.mark.parametrize("form", ["plain", "sums", "residual", "affine", "codes", "y_codes", "all"])
+def test_conv3x3_one_chunk(esb, tile, fill, H, W, K, form):
+    """64 input channels on the fewest images whose tiles of 256 or 128 pixels give each CU one:
+    more pixels would take the next larger tile (or, for codes, the resident filter)."""
+    cus = torch_cuda().cuda.get_device_properties(0).multi_processor_count
+    tiles = -(-cus // (K // 64))                   # of each channel tile
+    Nb = -(-((tiles - 1) * tile + 1) // (H * W))
+    assert -(-Nb * H * W // tile) * (K // 64) >= cus
+    assert tile == 256 or -(-Nb * H * W // 256) * (K // 64) < cus
+    step = 64 // (W + 2)                           # patch rows that the threads fill at once
+    span = (W - 1 + tile - 1) // W                 # output rows of a tile after its first
+    rows = span + 2 * ((H - 1 + span) // H) + 3
+    assert (5 if tile < 256 and -(-rows // step) <= 5 else 10) == fill
+    check_images(esb, Nb, H, W, 64, K, form, sorted({0, Nb // 2, Nb - 1}), 9300 + W + tile)
 
 
 @pytest.mark.parametrize("st,Nb,H,C,K", [(1, 5400, 56, 256, 64), (2, 45000, 14, 512, 64)])
