@@ -78,13 +78,8 @@ struct Conv3Params {
     int direct;                // outputs straight from the registers: 1 fp32, 2 codes, 0 neither
 };
 
-__device__ __forceinline__ uint32_t dec8(uint32_t c, const MmaDecode& d) {
-    const uint32_t t = (((c & d.lm) << d.shf) + d.inc) & d.lmf;   // exponent + 1 (mod 2^ebits)
-    return ((c << d.shs) & 0x80808080u) | t;                       // sign to bit 7
-}
-
 __device__ __forceinline__ uint4 dec16(uint4 v, const MmaDecode& d) {
-    return make_uint4(dec8(v.x, d), dec8(v.y, d), dec8(v.z, d), dec8(v.w, d));
+    return make_uint4(dec_f8(v.x, d), dec_f8(v.y, d), dec_f8(v.z, d), dec_f8(v.w, d));
 }
 
 // LDS byte offset of chunk c (0..3) of patch pixel pix.

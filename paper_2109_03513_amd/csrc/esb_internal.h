@@ -457,6 +457,12 @@ struct MmaDecode {
     int shf, shs;                         // fraction and sign shifts
 };
 MmaDecode mma_decode(const Fmt& f, int op);
+// Four codes (one per byte) to four OCP E4M3 values.
+__device__ __forceinline__ uint32_t dec_f8(uint32_t c, const MmaDecode& d) {
+    const uint32_t t = (((c & d.lm) << d.shf) + d.inc) & d.lmf;   // exponent + 1 (mod 2^ebits)
+    return ((c << d.shs) & 0x80808080u) | t;                       // sign to bit 7
+}
+
 // 1 (E4M3), 0 (int8 table) or -1 (not eligible) for this pair of formats and
 // reduction length.
 int mma_choose(const Fmt& fa, const Fmt& fb, int64_t K);

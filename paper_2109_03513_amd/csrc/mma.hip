@@ -122,11 +122,6 @@ __device__ __forceinline__ void post_epilogue(const FastParams& g, float* slab, 
     post_absmax_flush(g.post, amax);
 }
 
-__device__ __forceinline__ uint32_t dec_f8(uint32_t c, const MmaDecode& d) {
-    const uint32_t t = (((c & d.lm) << d.shf) + d.inc) & d.lmf;   // exponent + 1 (mod 2^ebits)
-    return ((c << d.shs) & 0x80808080u) | t;                       // sign to bit 7
-}
-
 // Four codes to four OCP E2M1 nibbles (low half of each byte), value q
 // exactly: the same exponent-field increment as dec_f8 on a 1-bit fraction.
 __device__ __forceinline__ uint32_t dec_f4(uint32_t c, const MmaDecode& d) {

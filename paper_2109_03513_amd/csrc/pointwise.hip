@@ -54,11 +54,6 @@ struct PwParams {
     int out_shift, kX, kW;
 };
 
-__device__ __forceinline__ uint32_t pw_dec(uint32_t c, const MmaDecode& d) {
-    const uint32_t t = (((c & d.lm) << d.shf) + d.inc) & d.lmf;   // exponent + 1 (mod 2^ebits)
-    return ((c << d.shs) & 0x80808080u) | t;                       // sign to bit 7
-}
-
 // V bytes of codes as V / 4 dwords.
 template <int V>
 __device__ __forceinline__ void pw_load(const uint8_t* p, uint32_t* d) {
@@ -121,7 +116,7 @@ __global__ __launch_bounds__(kPwThreads) void k_pw(PwParams p) {
                 const bool in = i < total && r < ncur && o < p.K;
                 pw_load<V>(p.w + (in ? (int64_t)(n0 + r) * p.ldw + o : 0), d[u]);
 #pragma unroll
-                for (int e = 0; e < DW; e++) d[u][e] = in ? pw_dec(d[u][e], p.dw) : 0u;
+                for (int e = 0; e < DW; e++) d[u][e] = in ? dec_f8(d[u][e], p.dw) : 0u;
             }
 #pragma unroll
             for (int u = 0; u < 4; u++) {
@@ -147,7 +142,7 @@ __global__ __launch_bounds__(kPwThreads) void k_pw(PwParams p) {
 #pragma unroll
         for (int ks = 0; ks < KS; ks++)
 #pragma unroll
-            for (int e = 0; e < 8; e++) xf[ks][e] = (int)pw_dec(raw[ks][e], p.dx);
+            for (int e = 0; e < 8; e++) xf[ks][e] = (int)dec_f8(raw[ks][e], p.dx);
         if (tile + 4 * (int)gridDim.x < p.tiles) fetch(tile + 4 * gridDim.x);
         // the residual of this lane's outputs, one channel block ahead
         f32x4 rnx[4];

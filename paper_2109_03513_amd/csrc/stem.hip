@@ -75,15 +75,6 @@ struct StemParams {
     uint32_t zero_code;        // the +0 code of the input format (outside the image)
 };
 
-__device__ __forceinline__ int decode_byte(uint32_t c, const DecodeInfo& d) {
-    c &= (1u << d.n) - 1u;
-    const uint32_t sg = (c >> (d.n - 1)) & 1u;
-    const uint32_t e = (c >> d.k) & (uint32_t)d.emax;
-    const uint32_t f = c & ((1u << d.k) - 1u);
-    const int m = (e == (uint32_t)d.emax) ? (int)f : (int)(((1u << d.k) | f) << e);
-    return sg ? -m : m;
-}
-
 // Four waves per SIMD: two workgroups share a CU (LDS and registers fit).
 template <int C>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 4)))
@@ -103,11 +94,11 @@ void k_stem(StemParams p) {
     // decode tables and the filter, once: the filter as 64 x RMAX rows of 32 bytes
     // (zero past S*C and for rows past R); lane l later reads the B fragment of
     // channel 32 half + l % 32, bytes 16 (l / 32) .. + 15 of the row of filter row r
-    if (tid < 256) xlut[tid] = (int8_t)decode_byte((uint32_t)tid, p.dx);
+    if (tid < 256) xlut[tid] = (int8_t)decode_one((uint32_t)tid, p.dx);
     for (int it = tid; it < KO * RMAX * 32; it += kThreads) {
         const int n = it / (RMAX * 32), r = (it / 32) % RMAX, j = it % 32;
         int m = 0;
-        if (r < R && j < SC) m = decode_byte(p.w[((int64_t)n * R + r) * SC + j], p.dw);
+        if (r < R && j < SC) m = decode_one(p.w[((int64_t)n * R + r) * SC + j], p.dw);
         wlds[n * WST + r * 32 + j] = (uint8_t)m;
     }
     const int boff = (32 * half + (lane & 31)) * WST + 16 * (lane >> 5);
