@@ -25,8 +25,11 @@
 //    current chunk's MFMAs run;
 //  * per tap one v_mfma_scale_f32_32x32x64_f8f6f4 per 32 x 32 block;
 //  * the epilogue is the contraction's: acc = the fp32 sum times 2^shift
-//    (an exact integer), y0 = fl32(s fl32(acc)) and the fused post-processing,
-//    four consecutive channels per lane after a round trip through LDS.
+//    (an exact integer), y0 = fl32(s fl32(acc)) and the fused post-processing.
+//    fp32 outputs alone and codes alone, without the affine step, leave straight
+//    from the accumulators (store_direct) where the kernel has an instance for
+//    them; every other form makes a round trip through LDS, four consecutive
+//    channels per lane.
 // The fp32 sums are exact under the same admission rule as the implicit-GEMM
 // fp8 path (every product at most 2^12, 9 C x the largest product < 2^24), so
 // the results equal that path's bit for bit.
@@ -342,8 +345,10 @@ __device__ __forceinline__ uint32_t store_direct(const Conv3Params& p, const v16
 // other chunk of input channels, each with its own patch and filter slice, and add their
 // (exact) sums at the end: where there are no more tiles than CUs, a second workgroup would
 // find no tile, and four waves alone leave fill, barriers and LDS reads uncovered
-// (512 -> 512 at 7 x 7, batch 64, 200 tiles: 28.0 us with KG 1, 25.6 with 2; with four chunks
-// each half has too few of them: 256 -> 256 at 14 x 14, batch 16, 14.4 against 14.8).
+// (512 -> 512 at 7 x 7, batch 64, 200 tiles: fp32 out 23.4 us with KG 1, 20.7 with 2; codes
+// 22.4 and 20.0; all outputs 29.8 and 25.1.  Six chunks, 384 -> 384 at 14 x 14, batch 16: 17.4
+// and 16.0.  Four chunks gain too little for instances of their own: 256 -> 256 at 14 x 14,
+// batch 16, codes 12.1 and 12.1, fp32 out 11.7 and 11.4).
 // FILL: patch chunks per thread, at least patch rows / rows per step; the unused ones of a
 // larger FILL cost registers, repeated loads of one place and decoding.
 template <int TMB, bool MULTI, int OUT, int FILL, int KG = 1>
@@ -404,7 +409,8 @@ void k_conv3x3(Conv3Params p) {
         nrows = i1 * PP2 + st * p1 + 3 - R0;
     };
     // This thread's patch chunks of a tile (chunk u is row fri + u rstep): their places in the
-    // input, and in bit u of vmask whether inside it; nfill: chunks that any thread has.
+    // input, and in bit u of vmask whether inside it (frows: the tile's patch rows; chunks
+    // outside the input or past the rows load the input's first bytes, unused).
     uint4 raw[FILL], wraw[kWPer];
     uint32_t poff[FILL], vmask = 0;
     int frows = 0;
@@ -914,7 +920,7 @@ bool tile_fits(int P, int Q, int TM, int H, int W, int st) {
 // input channels) whose tiles fit the patch and give at least one workgroup per
 // CU (half a workgroup per CU with several chunks: every tile streams the filter
 // slices again, so larger tiles halve that traffic per pixel; ResNet18 l4 at batch
-// 64, 200 tiles of 128 pixels against 392 of 64: 33.9 against 35.5 us), else the
+// 64, 200 tiles of 128 pixels against 392 of 64: 20.7 against 26.4 us), else the
 // smallest: one 56 x 56 image with 64 channels takes 10.4 us in 13 tiles of 256
 // pixels and 7.2 in 49 of 64, 256 channels at 14 x 14 16.2 and 13.7.
 int choose_tmb(int64_t M, int ntn, int P, int Q, int H, int W, int st, bool multi) {
