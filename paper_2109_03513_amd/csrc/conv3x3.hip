@@ -1074,7 +1074,7 @@ hipError_t launch_conv3x3(const ConvGeom& g, int K, const uint8_t* x, const Fmt&
     const int tmb = choose_tmb(p.M, p.ntn, g.P, g.Q, g.H, g.W, p.st, multi);
     if (tmb == 0) return hipErrorInvalidValue;
     p.ntm = (p.M + 32 * tmb - 1) / (32 * tmb);
-    // patch chunks per thread: 5 where they suffice (all but wide images), else kMaxFill
+    // patch chunks per thread: 5 where they suffice (most images of up to 30 columns), else more
     const int rstep = kThreads / (4 * (g.W + 2));
     const int fill = (patch_rows_max(g.P, g.Q, 32 * tmb, g.H, p.st) + rstep - 1) / rstep;
     const bool few = fill <= kFewFill;
