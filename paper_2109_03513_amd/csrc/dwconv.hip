@@ -397,8 +397,13 @@ static hipError_t launch_dw3(const ConvGeom& g, const uint8_t* x, const Fmt& fx,
 //  * else: lean outputs with ReLU or max|z| (5.8 / 5.4), y from 16 channels, codes and sums
 //    from 64, or over 2^18 (sums 2^19) outputs; other epilogues over 2^20 (affine and codes at 2^15
 //    6.8 / 10.1, at 2^20 11.3 / 10.0);
-//  * fewer than four columns, whole threads of padding: C % 16 == 0 alone, codes of single pixels,
-//    else 48 channels and more, 144 without post-processing or over 2048 outputs.
+//  * two or three columns, where threads are partly padding: C % 16 == 0 but for post-processing
+//    of less than 48 channels in three columns (2 x 2, 32 channels, batch 8, sums 5.9 / 5.2; 3 x 3,
+//    16 channels, affine and codes 9 % the other way); else large calls (100 channels at 3 x 3,
+//    batch 512, sums 6.5 / 5.9);
+//  * one column, three quarters padding: up to 3 x 10^5 outputs (codes 5 x 10^5: 144 channels, batch
+//    4096, 7.1 / 8.0) of C % 16 == 0 or 96 channels, without post-processing of 64 to 144 channels
+//    and more (batch 128, 96 channels, y 5.4 / 4.8; batch 1 5 % the other way).
 static bool dw3_fits(const ConvGeom& g, const uint8_t* x, const Fmt& fx, const Fmt& fw,
                      const int32_t* acc, const float* y, const Post* post) {
     const Post P = post ? *post : Post{};
@@ -406,9 +411,10 @@ static bool dw3_fits(const ConvGeom& g, const uint8_t* x, const Fmt& fx, const F
     const int64_t outputs = (int64_t)g.Nb * g.P * g.Q * g.C;
     bool pays;
     if (dw3_out(g, acc, y, P)) pays = c16 || (P.on && y) || g.C >= (y ? 16 : 64) || outputs >= 1 << 18;
-    else if (g.Q < 4 && !c16) pays = outputs >= 1 << 20;
-    else if (g.Q == 1) pays = P.codes || (outputs < 300000 && (P.on || g.C >= 144));
-    else if (g.Q < 4) pays = P.on ? g.C >= 48 : (g.C >= 144 || outputs >= 2048);
+    else if (g.Q == 1 && P.on) pays = (c16 || g.C >= 96) && outputs < (c16 && P.codes ? 500000 : 300000);
+    else if (g.Q == 1) pays = c16 && outputs < 300000 && (g.C >= 144 || (g.C >= 64 && outputs >= 3000));
+    else if (g.Q < 4 && c16) pays = g.Q == 2 || !P.on || g.C >= 48;
+    else if (g.Q < 4) pays = outputs >= (!P.on && g.C >= 64 ? 1 << 15 : (P.on && g.Q == 3 ? 1 << 20 : 1 << 19));
     else if (!P.on) pays = c16 || g.C >= 64 || outputs >= 1 << 19;
     else pays = (c16 && g.C >= (affine ? 192 : 64)) || outputs >= 1 << 20;
     return pays && g.R == 3 && g.S == 3 && g.sh == 1 && g.sw == 1 && g.C % 4 == 0 && fx.n <= 5 &&

@@ -124,7 +124,10 @@ def test_strip_heights(rows, form):
 @pytest.mark.parametrize("N,H,W,C", [
     (1, 9, 9, 60), (1, 9, 9, 64), (1, 9, 9, 16), (1, 9, 9, 12), (1, 9, 9, 176), (1, 9, 9, 192),
     (16, 64, 64, 4), (15, 64, 64, 4), (32, 64, 64, 4), (64, 64, 64, 4),
-    (4, 1, 1, 16), (4, 1, 1, 48), (3, 3, 3, 48), (3, 3, 3, 32), (100, 3, 3, 20)])
+    (4, 1, 1, 16), (4, 1, 1, 48), (3, 3, 3, 48), (3, 3, 3, 32), (100, 3, 3, 20),
+    (46, 1, 1, 64), (47, 1, 1, 64), (2083, 1, 1, 144), (2084, 1, 1, 144), (3472, 1, 1, 144), (3473, 1, 1, 144),
+    (5, 1, 1, 100), (3000, 1, 1, 100), (3, 2, 2, 32), (82, 2, 2, 100), (81, 2, 2, 100), (3641, 2, 2, 36),
+    (3640, 2, 2, 36), (1619, 3, 3, 36), (1618, 3, 3, 36), (3237, 3, 3, 36), (3236, 3, 3, 36)])
 @pytest.mark.parametrize("form", ["y", "relu_y", "codes", "sums", "residual", "all"])
 def test_routes(N, H, W, C, form):
     check_images(N, H, W, C, form, sorted({0, N // 2, N - 1}), 86)
