@@ -290,8 +290,9 @@ bool pw_general(int M, int N, int K, const int32_t* acc, const float* y, const P
     if (M < 8) return K < 16 || N <= 8 || (!al && K >= 64 && N <= 16);
     if (N < 32) return true;
     if (P.codes && y) {
-        if (M >= 50000 && ((N <= 160 && N != 128 && !al) || (N <= 64 && N % 4))) return true;
-        if (K < 16) return MN < 3000000;
+        const bool half = N > 32 && N <= 64 && K >= 16;    // a 64-channel tile, at least half full
+        if (M >= 50000 && ((N <= 160 && N % 64 && !al && !half) || (N <= 64 && N % 4 && (al || !half)))) return true;
+        if (K < 16) return MN < 3000000 || (M < 20000 && MN >= 6000000);
         if (N % 4) return MN >= 2048 && MN < 5600000;
         return N <= 44 && M >= 18000;
     }
@@ -302,8 +303,8 @@ bool pw_general(int M, int N, int K, const int32_t* acc, const float* y, const P
         return N <= 256 || (P.res ? MN < 2000000 : K <= 224);
     }
     if (M >= 20000 && (K <= 224 || (N <= 64 && M >= 80000))) return true;
-    if (!al) return MN >= 3000000;
-    if (K <= 128 && N >= 512) return MN >= 6000000;
+    if (!al) return MN >= 1000000;
+    if (K <= 128 && N >= 256) return MN >= 3000000;
     return (MN >= 25000000 && N >= 256) || (N <= 32 && M >= 45000);
 }
 
@@ -323,18 +324,21 @@ bool pw_fits(const ConvGeom& g, int M, int N, int groups, const uint8_t* x, cons
     // reductions of at least 64: their 128-channel rows leave in longer runs (64 -> 128 over
     // 50176 pixels 10.4 us there, 10.9 here, with a residual 15.2 against 16.4; 128 -> 256
     // likewise 18.6 against 20.4), and for more channels over the longest reductions, whose filter
-    // copies fill the LDS in several shares (256 -> 768 over 12544 pixels 17.8 against 22.2).
+    // copies fill the LDS in several shares (256 -> 768 over 12544 pixels 17.8 against 22.2; with
+    // ReLU from more outputs, 224 -> 1000 over 4704 14.7 against 12.6, over 6272 15.3 against 17.4).
     // Few rows, few channels and codes are faster here (64 -> 64 over 200704 24.2 against 16.1,
     // codes 37.7 against 14.3; 64 -> 256 over 3136 5.1 against 4.2).
     if (!P.codes && K % 16 == 0 && K >= 64 && (int64_t)M * K >= 600000) {
         if (N > 64 && N <= 512) return false;
-        if (N > 512 && K > 192 && M < 20000 && MN >= 4000000 && MN < 15000000) return false;
+        const bool relu = P.on && !P.res;
+        if (N > 512 && K > 192 && M < 20000 && MN >= (relu ? 5800000 : 4000000) && MN < 15000000) return false;
     }
     if (out == 0) return pw_general(M, N, K, acc, y, P);
     // Output rows 4 KB apart, 32 of which a store instruction meets, share few of the memory
-    // channels (8 -> 1024 over 50176 pixels 53 us there, 90 here); with the
+    // channels (8 -> 1024 over 50176 pixels 53 us there, 90 here, over 18816 25.4 and 31.1; 128 ->
+    // 1024 over 18816 35.2 and 31.0, over 37632 51.6 and 57.5); with the
     // post-processing those kernels are slower too.
-    if (!P.on && ldc % 1024 == 0 && MN >= 19000000 && K <= 192) return false;
+    if (!P.on && ldc % 1024 == 0 && MN >= (K < 64 ? 19000000 : 20000000) && K <= 192) return false;
     // Two output streams at once (64 -> 1024 over 12544 pixels 21.7 there, 34.1 here).
     return !(out == 3 && y && N > 64 && MN >= 3000000);
 }

@@ -149,7 +149,9 @@ def test_several_tiles_per_wave(N, K, gy, form):
 ROUTES = [
     (7, 24, 64), (8, 24, 64), (7, 8, 64), (5, 16, 200), (40, 31, 48), (40, 32, 48), (31, 9, 64), (33, 9, 64),
     (2344, 65, 256), (2343, 65, 256), (100, 40, 8), (3000, 200, 8), (3001, 200, 8), (700, 33, 128),
-    (20000, 36, 64), (19999, 36, 64), (46000, 32, 256), (1200, 1000, 96), (1203, 1001, 200)]
+    (20000, 36, 64), (19999, 36, 64), (46000, 32, 256), (1200, 1000, 96), (1203, 1001, 200),
+    (2500, 400, 24), (2499, 400, 24), (11719, 256, 64), (11718, 256, 64), (15000, 400, 8), (14999, 400, 8),
+    (50000, 64, 24), (50000, 50, 24), (50000, 50, 8)]
 
 
 @pytest.mark.parametrize("M,N,K", ROUTES)
